@@ -9,18 +9,24 @@
 // (host key, bytes, rate, bucket) per bulk flow of a registered site to its
 // workgroup's staging range, and four kernels finish the job with no
 // per-flow device atomics:
-//   1. host_count_kernel: per classify workgroup, the number of its entries
+//   1. part_count_kernel: per classify workgroup, the number of its entries
 //      in each of P partitions (a partition is the top bits of a hash of the
 //      key, so all entries of a host land in one partition);
-//   2. host_scan_kernel: for each partition, the offset of every workgroup's
+//   2. part_scan_kernel: for each partition, the offset of every workgroup's
 //      share within the partition (a column prefix sum) and the totals;
-//   3. host_scatter_kernel: every entry to its partition's range;
-//   4. host_reduce_kernel: one workgroup per partition gathers its hosts in
-//      an LDS hash map with their statistics (LDS atomics), then finds each
-//      host's lower median bucket (the ceil(N/2)-th smallest of its N flows'
-//      buckets) by a radix selection over the 14-bit bucket: four rounds,
-//      each counting the candidates' next 4-bit digit in 16 LDS bins per
-//      host and keeping the digit where the running count reaches the rank.
+//   3. part_scatter_kernel: every entry to its partition's range;
+//   4. host_reduce_kernel: a group of lanes per partition gathers its hosts
+//      in an LDS hash map with their statistics (LDS atomics), then finds
+//      each host's lower median bucket (the ceil(N/2)-th smallest of its N
+//      flows' buckets).  Up to 2,048 entries (nearly every partition): the
+//      map has 512 slots, the flow count's atomic gives each flow its place
+//      in its host's list, the lists are packed into LDS, and every flow is
+//      ranked within its host's list by a lane (lists beyond 256 flows are
+//      bisected by a wave).  More entries (a hot host): a map of 256 slots
+//      and a radix selection over the 14-bit bucket, four rounds that re-read
+//      the entries, each counting the candidates' next 4-bit digit in 16 LDS
+//      bins per host and keeping the digit where the running count reaches
+//      the rank.
 //      A partition with more hosts than the map holds is done in batches: the
 //      entries of hosts not yet in the map are compacted in place and
 //      reduced by the next batch.
@@ -41,9 +47,15 @@ namespace gnm {
 
 namespace {
 
-constexpr uint32_t kHostThreads = 256;
-constexpr uint32_t kHostSlots = 256;        // LDS hash-map slots per reduce workgroup (a power of two)
-constexpr uint32_t kEntryCap = 2048;        // entries of a partition whose (slot, bucket) stay in LDS
+constexpr uint32_t kHostThreads = 256;  // lanes that reduce one partition
+constexpr uint32_t kHostGroups = 2;     // partitions reduced by one workgroup
+constexpr uint32_t kHostSlots = 256;        // LDS hash-map slots of a large partition (a power of two)
+constexpr uint32_t kListSlots = 512;        // of one whose flow lists fit LDS: the partition rule's mean of 300 or
+                                            // fewer entries, all of different hosts, must not need a second batch
+constexpr uint32_t kListCap = 2048;         // entries of such a partition
+constexpr uint32_t kListRank = 256;         // flows of a host that are ranked one against the others
+constexpr uint32_t kListSlotBits = 9, kListPlaceBits = 9;
+static_assert(kListSlots == 1u << kListSlotBits && kListRank <= 1u << kListPlaceBits, "list words");
 constexpr uint64_t kHostEmpty = ~0ull;      // free map slot (no key has all low 32 bits set)
 constexpr uint32_t kDigitBins = 16;         // radix selection: 4 bits per round
 constexpr uint32_t kDigitRounds = 4;        // buckets < 2^14: digits at bits 12, 8, 4, 0
@@ -94,29 +106,29 @@ struct HostMap {
   uint32_t out[kHostSlots];     // output index of the slot's host within the batch
 };
 
-__device__ __forceinline__ uint32_t slot_hash(u64 key) { return (uint32_t)mix64(key) & (kHostSlots - 1u); }
-
-// Slot of key in the map, inserting it when absent; kNoSlot when the map is
-// full.  Keys are never removed within a batch, so a slot seen holding
-// another key stays that way and linear probing needs no locks.
-__device__ __forceinline__ uint32_t map_insert(HostMap &m, u64 key) {
-  uint32_t s = slot_hash(key);
-  for (uint32_t probe = 0; probe < kHostSlots; ++probe) {
-    u64 cur = m.key[s];
-    if (cur == kHostEmpty) cur = atomicCAS(&m.key[s], kHostEmpty, key);
+// Slot of key in a map of SLOTS keys, inserting it when absent; kNoSlot when
+// the map is full.  Keys are never removed within a batch, so a slot seen
+// holding another key stays that way and linear probing needs no locks.
+template <uint32_t SLOTS>
+__device__ __forceinline__ uint32_t map_insert(u64 *keys, u64 key) {
+  uint32_t s = (uint32_t)mix64(key) & (SLOTS - 1u);
+  for (uint32_t probe = 0; probe < SLOTS; ++probe) {
+    u64 cur = keys[s];
+    if (cur == kHostEmpty) cur = atomicCAS(&keys[s], kHostEmpty, key);
     if (cur == kHostEmpty || cur == key) return s;
-    s = (s + 1u) & (kHostSlots - 1u);
+    s = (s + 1u) & (SLOTS - 1u);
   }
   return kNoSlot;
 }
 
-__device__ __forceinline__ uint32_t map_find(const HostMap &m, u64 key) {
-  uint32_t s = slot_hash(key);
-  for (uint32_t probe = 0; probe < kHostSlots; ++probe) {
-    const u64 cur = m.key[s];
+template <uint32_t SLOTS>
+__device__ __forceinline__ uint32_t map_find(const u64 *keys, u64 key) {
+  uint32_t s = (uint32_t)mix64(key) & (SLOTS - 1u);
+  for (uint32_t probe = 0; probe < SLOTS; ++probe) {
+    const u64 cur = keys[s];
     if (cur == key) return s;
     if (cur == kHostEmpty) return kNoSlot;
-    s = (s + 1u) & (kHostSlots - 1u);
+    s = (s + 1u) & (SLOTS - 1u);
   }
   return kNoSlot;
 }
@@ -145,137 +157,363 @@ __device__ __forceinline__ void pick_digit(HostMap &m, uint32_t s) {
 
 constexpr uint32_t kPerThread = 4;  // entries a thread loads before working on them
 
-// One workgroup per partition.  A partition of at most kEntryCap entries
-// keeps each entry's (slot, bucket) in LDS after the first pass, so the
-// three later digit rounds read no device memory; a larger one (a hot host)
-// re-reads its entries and looks their keys up again.
-__global__ __launch_bounds__(kHostThreads) void host_reduce_kernel(const Parts q) {
+// The map of a partition of at most kListCap entries.  stat: bytes, rate sum,
+// minimum and maximum of each slot's host.
+struct ListMap {
+  u64 key[kListSlots];
+  u64 stat[4][kListSlots];
+  uint32_t flows[kListSlots];
+  uint16_t base[kListSlots];    // first list element
+  uint16_t slot[kListSlots];    // slot of the batch's i-th host
+  uint16_t median[kListSlots];  // of each slot's host
+  // flows, host by host: bucket << 18 | place among the host's flows (modulo
+  // 512) << 9 | slot, so the words of a list of at most 512 are distinct and
+  // ordered by bucket
+  uint32_t list[kListCap];
+  uint16_t queue[kListCap / kListRank];  // slots of longer lists
+};
+
+union Maps {
+  HostMap big;
+  ListMap list;
+};
+
+// What the groups of a workgroup share.  Every group takes every barrier, so
+// loops around barriers run to the largest n of the workgroup.
+struct Shared {
+  uint32_t overflow[kHostGroups], deferred[kHostGroups], queued[kHostGroups];
+  uint32_t wave[kHostGroups][kHostThreads / 64];
+  uint32_t n[kHostGroups];
+  u64 out[kHostGroups];
+};
+
+// Entries of hosts that found no slot, compacted to the front for the next
+// batch: each round reads a block of entries, waits, then writes them at or
+// before the block's end, so no entry is overwritten unread.
+template <uint32_t SLOTS>
+__device__ __forceinline__ void compact_deferred(HostEntry *ent, uint32_t n, uint32_t nmax, const u64 *keys,
+                                                 uint32_t *deferred, uint32_t tid) {
+  for (uint32_t i0 = 0; i0 < nmax; i0 += kHostThreads) {
+    const uint32_t i = i0 + tid;
+    u64 key = 0, by = 0, rt = 0;
+    uint32_t bk = 0;
+    bool keep = false;
+    if (i < n) {
+      load_entry(ent + i, key, by, rt, bk);
+      keep = map_find<SLOTS>(keys, key) == kNoSlot;
+    }
+    __syncthreads();
+    if (keep) store_entry(ent + atomicAdd(deferred, 1u), key, by, rt, bk);
+    __syncthreads();
+  }
+}
+
+// Output indexes for the groups' hosts with one device atomic for the
+// workgroup: the atomics of all partitions go to one counter, so each costs
+// the chip about 6 ns (4,096 of them took 25 of the kernel's 67 us).
+// reserve_out (one thread; sh.wave[g] holds the waves' host counts, in the
+// bits from `shift`) starts it, publish_out leaves each group's first index
+// in sh.out once its round trip has been covered.
+__device__ __forceinline__ u64 reserve_out(const Shared &sh, const Parts &q, uint32_t shift) {
+  u64 all = 0;
+#pragma unroll
+  for (uint32_t g = 0; g < kHostGroups; ++g)
+#pragma unroll
+    for (uint32_t v = 0; v < kHostThreads / 64u; ++v) all += sh.wave[g][v] >> shift;
+  return all ? __hip_atomic_fetch_add(&q.counters[0], all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+}
+
+__device__ __forceinline__ void publish_out(Shared &sh, u64 out, uint32_t shift) {
+#pragma unroll
+  for (uint32_t g = 0; g < kHostGroups; ++g) {
+    sh.out[g] = out;
+#pragma unroll
+    for (uint32_t v = 0; v < kHostThreads / 64u; ++v) out += sh.wave[g][v] >> shift;
+  }
+}
+
+__device__ __forceinline__ bool any_overflow(const Shared &sh) {
+  uint32_t any = 0;
+#pragma unroll
+  for (uint32_t g = 0; g < kHostGroups; ++g) any |= sh.overflow[g];
+  return any != 0u;
+}
+
+// One batch of group g's partition of n <= kListCap entries; the entries left
+// to the next batch are counted in sh.deferred[g].
+__device__ __forceinline__ void reduce_lists(ListMap &m, Shared &sh, const Parts &q, HostEntry *ent, uint32_t n,
+                                             uint32_t nmax, uint32_t g) {
+  constexpr uint32_t kRounds = kListCap / (kPerThread * kHostThreads);
+  const uint32_t tid = threadIdx.x % kHostThreads, lane = tid % 64u, wv = tid / 64u;
+  for (uint32_t s = tid; s < kListSlots; s += kHostThreads) {
+    m.key[s] = kHostEmpty;
+    m.flows[s] = 0u;
+    m.stat[0][s] = m.stat[1][s] = m.stat[3][s] = 0;
+    m.stat[2][s] = ~0ull;
+  }
+  if (tid == 0) {
+    sh.overflow[g] = 0u;
+    sh.deferred[g] = 0u;
+    sh.queued[g] = 0u;
+  }
+  __syncthreads();
+  // hosts and statistics; every entry keeps (slot << 14 | bucket) and its
+  // place among its host's flows in registers
+  uint32_t sb[kRounds * kPerThread], place[kRounds * kPerThread];
+#pragma unroll
+  for (uint32_t r = 0; r < kRounds; ++r) {
+    if (r * kPerThread * kHostThreads >= n) break;
+    u64 key[kPerThread], by[kPerThread], rt[kPerThread];
+    uint32_t bk[kPerThread];
+#pragma unroll
+    for (uint32_t j = 0; j < kPerThread; ++j) {
+      const uint32_t i = (r * kPerThread + j) * kHostThreads + tid;
+      if (i < n) load_entry(ent + i, key[j], by[j], rt[j], bk[j]);
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kPerThread; ++j) {
+      const uint32_t e = r * kPerThread + j, i = e * kHostThreads + tid;
+      sb[e] = kNoSlot;
+      if (i >= n) continue;
+      const uint32_t s = map_insert<kListSlots>(m.key, key[j]);
+      if (s == kNoSlot) {
+        sh.overflow[g] = 1u;
+        continue;
+      }
+      sb[e] = (s << 14) | bk[j];
+      place[e] = atomicAdd(&m.flows[s], 1u);
+      atomicAdd(&m.stat[0][s], by[j]);
+      atomicAdd(&m.stat[1][s], rt[j]);
+      atomicMin(&m.stat[2][s], rt[j]);
+      atomicMax(&m.stat[3][s], rt[j]);
+    }
+  }
+  __syncthreads();
+  // slots 2 tid and 2 tid + 1: where their lists start and their places among
+  // the batch's hosts (one scan of hosts << 16 | flows)
+  static_assert(kListSlots == 2u * kHostThreads, "two slots per thread");
+  const uint32_t c0 = m.flows[2u * tid], c1 = m.flows[2u * tid + 1u];
+  const uint32_t mine = c0 + c1 + (c0 ? 1u << 16 : 0u) + (c1 ? 1u << 16 : 0u);
+  uint32_t x = mine;
+#pragma unroll
+  for (uint32_t o = 1; o < 64u; o <<= 1) {
+    const uint32_t y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63u) sh.wave[g][wv] = x;
+  __syncthreads();
+  uint32_t before = x - mine, all = 0;
+#pragma unroll
+  for (uint32_t v = 0; v < kHostThreads / 64u; ++v) {
+    before += v < wv ? sh.wave[g][v] : 0u;
+    all += sh.wave[g][v];
+  }
+  const uint32_t hosts = all >> 16, b0 = before & 0xFFFFu, b1 = b0 + c0;
+  const uint32_t h0 = before >> 16, h1 = h0 + (c0 ? 1u : 0u);
+  m.base[2u * tid] = (uint16_t)b0;
+  m.base[2u * tid + 1u] = (uint16_t)b1;
+  if (c0) m.slot[h0] = (uint16_t)(2u * tid);
+  if (c1) m.slot[h1] = (uint16_t)(2u * tid + 1u);
+  __syncthreads();
+  // the batch's output indexes: the round trip overlaps the lists
+  u64 first = 0;
+  if (threadIdx.x == 0) first = reserve_out(sh, q, 16u);
+#pragma unroll
+  for (uint32_t e = 0; e < kRounds * kPerThread; ++e) {
+    if (e * kHostThreads >= n) break;
+    if (e * kHostThreads + tid < n && sb[e] != kNoSlot) {
+      const uint32_t sl = sb[e] >> 14, bk = sb[e] & 0x3FFFu;
+      m.list[m.base[sl] + place[e]] =
+          (bk << (kListSlotBits + kListPlaceBits)) | ((place[e] & ((1u << kListPlaceBits) - 1u)) << kListSlotBits) | sl;
+    }
+  }
+  __syncthreads();
+  // lower medians: a lane per flow counts the flows below it in its list; the
+  // one with the median's rank writes it.  Neighbouring lanes mostly share a
+  // list, so their reads are broadcasts.
+  const uint32_t flows = all & 0xFFFFu;
+  for (uint32_t i = tid; i < flows; i += kHostThreads) {
+    const uint32_t w = m.list[i], sl = w & (kListSlots - 1u);
+    const uint32_t c = m.flows[sl], *l = m.list + m.base[sl];
+    uint32_t below = 0;
+    if (c > kListRank) {
+      if (l == m.list + i) m.queue[atomicAdd(&sh.queued[g], 1u)] = (uint16_t)sl;
+      continue;
+    }
+    uint32_t k = 0;
+    for (; k + 4u <= c; k += 4u)
+      below += (uint32_t)(l[k] < w) + (uint32_t)(l[k + 1u] < w) + (uint32_t)(l[k + 2u] < w) + (uint32_t)(l[k + 3u] < w);
+    for (; k < c; ++k) below += l[k] < w;
+    if (below + 1u == (c + 1u) / 2u) m.median[sl] = (uint16_t)(w >> (kListSlotBits + kListPlaceBits));
+  }
+  __syncthreads();
+  const uint32_t queued = sh.queued[g];
+  for (uint32_t j = wv; j < queued; j += kHostThreads / 64u) {
+    // the smallest bucket with at least `want` flows at or below it
+    const uint32_t sl = m.queue[j], c = m.flows[sl], base = m.base[sl], want = (c + 1u) / 2u;
+    uint32_t lo = 0, hi = (1u << 14) - 1u;
+    while (lo < hi) {
+      const uint32_t mid = (lo + hi) / 2u;
+      uint32_t cnt = 0;
+      for (uint32_t k = lane; k - lane < c; k += 64u)
+        cnt += (uint32_t)__popcll(
+            __ballot(k < c && (m.list[base + (k < c ? k : 0u)] >> (kListSlotBits + kListPlaceBits)) <= mid));
+      if (cnt >= want) hi = mid;
+      else lo = mid + 1u;
+    }
+    if (lane == 0) m.median[sl] = (uint16_t)lo;
+  }
+  if (threadIdx.x == 0) publish_out(sh, first, 16u);
+  __syncthreads();
+  // the batch's hosts, consecutive lanes on consecutive words
+  const u64 out = sh.out[g];
+  const u64 room = q.capacity > out ? q.capacity - out : 0ull;
+  const uint32_t put = hosts < room ? hosts : (uint32_t)room;
+  for (uint32_t i = tid; i < put; i += kHostThreads) {
+    q.keys[out + i] = m.key[m.slot[i]];
+    if (q.median) q.median[out + i] = m.median[m.slot[i]];
+  }
+  for (uint32_t i = tid; i < 5u * put; i += kHostThreads) {
+    const uint32_t h = i / 5u, f = i - 5u * h, s = m.slot[h];
+    q.stats[5u * out + i] = f == 0u ? (u64)m.flows[s] : m.stat[f - 1u][s];
+  }
+  compact_deferred<kListSlots>(ent, sh.overflow[g] ? n : 0u, any_overflow(sh) ? nmax : 0u, m.key, &sh.deferred[g], tid);
+}
+
+// One batch of a larger partition (a hot host): every digit round re-reads
+// the entries and looks their keys up again.
+__device__ __forceinline__ void reduce_radix(HostMap &m, Shared &sh, const Parts &q, HostEntry *ent, uint32_t n,
+                                             uint32_t nmax, uint32_t g) {
   static_assert(kHostSlots == kHostThreads, "one map slot per thread");
-  __shared__ HostMap m;
-  __shared__ uint32_t e_sb[kEntryCap];  // slot << 14 | bucket, kNoSlot for a host left to the next batch
-  __shared__ uint32_t s_overflow, s_deferred, s_wave[kHostThreads / 64];
-  __shared__ u64 s_out;
-  const uint32_t p = blockIdx.x, tid = threadIdx.x, lane = tid % 64u, wv = tid / 64u;
+  const uint32_t tid = threadIdx.x % kHostThreads, lane = tid % 64u, wv = tid / 64u;
+  m.key[tid] = kHostEmpty;
+  m.flows[tid] = 0u;
+  m.bytes[tid] = m.rsum[tid] = m.rmax[tid] = 0;
+  m.rmin[tid] = ~0ull;
+  m.prefix[tid] = 0u;
+#pragma unroll
+  for (uint32_t j = 0; j < kDigitBins; ++j) m.bins[j][tid] = 0u;
+  if (tid == 0) {
+    sh.overflow[g] = 0u;
+    sh.deferred[g] = 0u;
+  }
+  __syncthreads();
+  // hosts, statistics and the first digit (bits 13..12) of every bucket;
+  // each thread loads kPerThread entries before it works on them
+  for (uint32_t i0 = 0; i0 < n; i0 += kPerThread * kHostThreads) {
+    u64 key[kPerThread], by[kPerThread], rt[kPerThread];
+    uint32_t bk[kPerThread];
+#pragma unroll
+    for (uint32_t j = 0; j < kPerThread; ++j) {
+      const uint32_t i = i0 + j * kHostThreads + tid;
+      if (i < n) load_entry(ent + i, key[j], by[j], rt[j], bk[j]);
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kPerThread; ++j) {
+      const uint32_t i = i0 + j * kHostThreads + tid;
+      if (i >= n) continue;
+      const uint32_t s = map_insert<kHostSlots>(m.key, key[j]);
+      if (s == kNoSlot) {
+        sh.overflow[g] = 1u;
+        continue;
+      }
+      atomicAdd(&m.flows[s], 1u);
+      atomicAdd(&m.bytes[s], (u64)by[j]);
+      atomicAdd(&m.rsum[s], (u64)rt[j]);
+      atomicMin(&m.rmin[s], (u64)rt[j]);
+      atomicMax(&m.rmax[s], (u64)rt[j]);
+      atomicAdd(&m.bins[bk[j] >> 12][s], 1u);
+    }
+  }
+  __syncthreads();
+  // reserve the batch's output indexes now, so the atomic's round trip
+  // overlaps the digit rounds
+  const bool used = m.key[tid] != kHostEmpty;
+  const u64 bal = __ballot(used);
+  if (lane == 0) sh.wave[g][wv] = (uint32_t)__popcll(bal);
+  if (used) m.want[tid] = (m.flows[tid] + 1u) / 2u;
+  __syncthreads();
+  u64 first = 0;
+  if (threadIdx.x == 0) first = reserve_out(sh, q, 0u);
+  if (used) {
+    pick_digit(m, tid);
+    uint32_t before = (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+    for (uint32_t v = 0; v < wv; ++v) before += sh.wave[g][v];
+    m.out[tid] = before;
+  }
+  __syncthreads();
+  // the other three digits, among the candidates that share the digits so far
+  for (uint32_t r = 1; r < kDigitRounds; ++r) {
+    const uint32_t shift = 12u - 4u * r;
+    for (uint32_t i = tid; i < n; i += kHostThreads) {
+      uint32_t bk;
+      u64 key, by, rate;
+      load_entry(ent + i, key, by, rate, bk);
+      const uint32_t s = map_find<kHostSlots>(m.key, key);
+      if (s == kNoSlot) continue;
+      if ((bk >> (shift + 4u)) == m.prefix[s]) atomicAdd(&m.bins[(bk >> shift) & 15u][s], 1u);
+    }
+    __syncthreads();
+    if (used) pick_digit(m, tid);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) publish_out(sh, first, 0u);
+  __syncthreads();
+  // write the batch's hosts
+  if (used) {
+    const uint64_t idx = sh.out[g] + m.out[tid];
+    if (idx < q.capacity) {
+      q.keys[idx] = m.key[tid];
+      u64 *st = q.stats + idx * 5u;
+      st[0] = m.flows[tid];
+      st[1] = m.bytes[tid];
+      st[2] = m.rsum[tid];
+      st[3] = m.rmin[tid];
+      st[4] = m.rmax[tid];
+      if (q.median) q.median[idx] = m.prefix[tid];
+    }
+  }
+  compact_deferred<kHostSlots>(ent, sh.overflow[g] ? n : 0u, any_overflow(sh) ? nmax : 0u, m.key, &sh.deferred[g], tid);
+}
+
+// One workgroup per kHostGroups partitions, a group of kHostThreads lanes for
+// each.  Small partitions take batches of lists together; large ones then
+// batches of the radix selection.
+// A window of 10 M records (4,096 partitions of 344 entries, 127 hosts) is
+// bound by the latency of a workgroup's steps and by the one counter:
+// 61.7 us with a radix selection for every partition; with lists 67 us at one
+// partition per workgroup (42 without the counter's atomics), 51.7 at two,
+// 56 at four (whose barriers wait for the slowest of four).  One of 1 M
+// records of the 64-site registry (512 partitions of 275 entries, nearly as
+// many hosts): 49 us when its hosts overflowed a map of 256 slots, 11.7 now.
+__global__ __launch_bounds__(kHostThreads * kHostGroups) void host_reduce_kernel(const Parts q) {
+  __shared__ Maps m[kHostGroups];
+  __shared__ Shared sh;
+  const uint32_t g = threadIdx.x / kHostThreads, p = blockIdx.x * kHostGroups + g;
   HostEntry *ent = q.part + q.pbase[p];
   uint32_t n = q.ptotal[p];
-  while (n > 0) {
-    const bool in_lds = n <= kEntryCap;
-    m.key[tid] = kHostEmpty;
-    m.flows[tid] = 0u;
-    m.bytes[tid] = m.rsum[tid] = m.rmax[tid] = 0;
-    m.rmin[tid] = ~0ull;
-    m.prefix[tid] = 0u;
+  for (;;) {
+    if (threadIdx.x % kHostThreads == 0) sh.n[g] = n;
+    __syncthreads();
+    uint32_t nlist = 0, nbig = 0;  // largest of either kind
 #pragma unroll
-    for (uint32_t j = 0; j < kDigitBins; ++j) m.bins[j][tid] = 0u;
-    if (tid == 0) {
-      s_overflow = 0u;
-      s_deferred = 0u;
+    for (uint32_t v = 0; v < kHostGroups; ++v) {
+      const uint32_t x = sh.n[v];
+      if (x <= kListCap) nlist = x > nlist ? x : nlist;
+      else nbig = x > nbig ? x : nbig;
     }
-    __syncthreads();
-    // hosts, statistics and the first digit (bits 13..12) of every bucket;
-    // each thread loads kPerThread entries before it works on them
-    for (uint32_t i0 = 0; i0 < n; i0 += kPerThread * kHostThreads) {
-      u64 key[kPerThread], by[kPerThread], rt[kPerThread];
-      uint32_t bk[kPerThread];
-#pragma unroll
-      for (uint32_t j = 0; j < kPerThread; ++j) {
-        const uint32_t i = i0 + j * kHostThreads + tid;
-        if (i < n) load_entry(ent + i, key[j], by[j], rt[j], bk[j]);
-      }
-#pragma unroll
-      for (uint32_t j = 0; j < kPerThread; ++j) {
-        const uint32_t i = i0 + j * kHostThreads + tid;
-        if (i >= n) continue;
-        const uint32_t s = map_insert(m, key[j]);
-        if (in_lds) e_sb[i] = s == kNoSlot ? kNoSlot : (s << 14) | bk[j];
-        if (s == kNoSlot) {
-          s_overflow = 1u;
-          continue;
-        }
-        atomicAdd(&m.flows[s], 1u);
-        atomicAdd(&m.bytes[s], (u64)by[j]);
-        atomicAdd(&m.rsum[s], (u64)rt[j]);
-        atomicMin(&m.rmin[s], (u64)rt[j]);
-        atomicMax(&m.rmax[s], (u64)rt[j]);
-        atomicAdd(&m.bins[bk[j] >> 12][s], 1u);
-      }
-    }
-    __syncthreads();
-    // reserve the batch's output indexes now, so the atomic's round trip
-    // overlaps the digit rounds
-    const bool used = m.key[tid] != kHostEmpty;
-    const u64 bal = __ballot(used);
-    if (lane == 0) s_wave[wv] = (uint32_t)__popcll(bal);
-    if (used) m.want[tid] = (m.flows[tid] + 1u) / 2u;
-    __syncthreads();
-    if (tid == 0) {
-      uint32_t t = 0;
-      for (uint32_t v = 0; v < kHostThreads / 64u; ++v) {
-        const uint32_t c = s_wave[v];
-        s_wave[v] = t;
-        t += c;
-      }
-      s_out = t ? __hip_atomic_fetch_add(&q.counters[0], (u64)t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
-    }
-    if (used) {
-      pick_digit(m, tid);
-      m.out[tid] = (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));  // plus s_wave[wv], known after the barrier
-    }
-    __syncthreads();
-    // the other three digits, among the candidates that share the digits so far
-    for (uint32_t r = 1; r < kDigitRounds; ++r) {
-      const uint32_t shift = 12u - 4u * r;
-      for (uint32_t i = tid; i < n; i += kHostThreads) {
-        uint32_t s, bk;
-        if (in_lds) {
-          const uint32_t sb = e_sb[i];
-          s = sb == kNoSlot ? kNoSlot : sb >> 14;
-          bk = sb & 0x3FFFu;
-        } else {
-          u64 key, by, rate;
-          load_entry(ent + i, key, by, rate, bk);
-          s = map_find(m, key);
-        }
-        if (s == kNoSlot) continue;
-        if ((bk >> (shift + 4u)) == m.prefix[s]) atomicAdd(&m.bins[(bk >> shift) & 15u][s], 1u);
-      }
+    if (nlist) {
+      const uint32_t mine = n <= kListCap ? n : 0u;
+      reduce_lists(m[g].list, sh, q, ent, mine, nlist, g);
       __syncthreads();
-      if (used) pick_digit(m, tid);
+      if (n <= kListCap) n = sh.deferred[g];
+    } else if (nbig) {
+      reduce_radix(m[g].big, sh, q, ent, n, nbig, g);
       __syncthreads();
+      n = sh.deferred[g];
+    } else {
+      return;
     }
-    // write the batch's hosts
-    if (used) {
-      const uint64_t idx = s_out + s_wave[wv] + m.out[tid];
-      if (idx < q.capacity) {
-        q.keys[idx] = m.key[tid];
-        u64 *st = q.stats + idx * 5u;
-        st[0] = m.flows[tid];
-        st[1] = m.bytes[tid];
-        st[2] = m.rsum[tid];
-        st[3] = m.rmin[tid];
-        st[4] = m.rmax[tid];
-        if (q.median) q.median[idx] = m.prefix[tid];
-      }
-    }
-    if (!s_overflow) break;
-    // entries of hosts that found no slot, compacted to the front for the
-    // next batch: each round reads a block of entries, waits, then writes
-    // them at or before the block's end, so no entry is overwritten unread
-    for (uint32_t i0 = 0; i0 < n; i0 += kHostThreads) {
-      const uint32_t i = i0 + tid;
-      u64 key = 0, by = 0, rt = 0;
-      uint32_t bk = 0;
-      bool keep = false;
-      if (i < n) {
-        load_entry(ent + i, key, by, rt, bk);
-        keep = in_lds ? e_sb[i] == kNoSlot : map_find(m, key) == kNoSlot;
-      }
-      __syncthreads();
-      if (keep) store_entry(ent + atomicAdd(&s_deferred, 1u), key, by, rt, bk);
-      __syncthreads();
-    }
-    n = s_deferred;
-    __syncthreads();
   }
 }
 
@@ -345,7 +583,8 @@ int host_pipeline_launch(const gnm_host_table *ht, uint64_t n, uint64_t grid, bo
                        pa, hp);
     hipLaunchKernelGGL((part_scatter_kernel<HostEntry, HostPart>), dim3((uint32_t)grid), dim3(kPartThreads),
                        P * 4u, stream, pa, hp);
-    hipLaunchKernelGGL(host_reduce_kernel, dim3(P), dim3(kHostThreads), 0, stream, q);
+    static_assert((1u << kPartBitsMin) % kHostGroups == 0, "whole workgroups");
+    hipLaunchKernelGGL(host_reduce_kernel, dim3(P / kHostGroups), dim3(kHostThreads * kHostGroups), 0, stream, q);
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
