@@ -14,7 +14,7 @@ SOURCES = ["registry.cpp", "kernels.hip", "hist.hip", "hosts.hip", "table.hip", 
 HEADERS = [os.path.join(INCLUDE, "gnm.h"), os.path.join(CSRC, "gnm_internal.h"),
            os.path.join(CSRC, "registry.h"), os.path.join(CSRC, "gnm_device.h"), os.path.join(CSRC, "hist.h"),
            os.path.join(CSRC, "hosts.h"),
-           os.path.join(CSRC, "partition.h"), os.path.join(CSRC, "table.h")]
+           os.path.join(CSRC, "partition.h"), os.path.join(CSRC, "rate.h"), os.path.join(CSRC, "table.h")]
 
 # Packed FP32 instructions are kept off for every device pass.
 DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

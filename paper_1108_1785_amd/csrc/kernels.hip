@@ -43,6 +43,7 @@
 #include "gnm_device.h"
 #include "hist.h"
 #include "hosts.h"
+#include "rate.h"
 #include "registry.h"
 #include "table.h"
 
@@ -100,9 +101,10 @@ struct ClassifyArgs {
   uint32_t lds_off_hist, hist_slots;  // LDS histogram cache (0 slots: every count goes to device memory)
   HostEntry *hs_entry;                // per-host staging (FEAT & kFeatHosts): workgroup b's entries
   uint32_t *hs_count;                 //   at [lo_b, lo_b + hs_count[b]) of its record slice [lo_b, hi_b)
-  TableEntry *ts_entry;               // spilled rows (a table beyond LDS, with a workspace; NULL: device
-  uint32_t *ts_count;                 //   atomics): workgroup b's entries at [s_b, s_b + ts_count[b]),
-  uint32_t ts_extra;                  //   s_b = lo_b + b * ts_extra, room for hi_b - lo_b + ts_extra
+  char *ts_entry;                     // spilled rows (a table beyond LDS, with a workspace; NULL: device
+  uint32_t *ts_count;                 //   atomics): workgroup b's range starts kTableRangeBytes * (lo_b +
+  uint32_t ts_extra, ts_tiles;        //   b * ts_extra) bytes in and has ts_tiles parts; counts [grid][ts_tiles]
+  uint32_t lds_off_tc;                //   LDS cursors of the parts
   uint32_t *ks_key;                   // staged histogram keys (FEAT & kFeatHist, with a workspace; NULL: the
   uint32_t *ks_count;                 //   LDS cache and device atomics): workgroup b's at [lo_b, lo_b + ks_count[b])
   uint32_t *kp_hist;                  // staged keys counted per partition here: [grid][kp_parts] (NULL: not here)
@@ -270,33 +272,6 @@ __device__ __forceinline__ void lookup_sites(const uint32_t (&ip)[R], const uint
   }
 }
 
-// floor(b * 8000 / d) for b with 8000*b < 2^53, d >= 1.
-constexpr uint64_t kFastBytesMax = ((1ull << 53) - 1ull) / 8000ull;
-
-__device__ __noinline__ uint64_t rate_bps_wide(uint64_t b, uint32_t d) {
-  // floor(8000 b / d) = 8000 floor(b/d) + floor(8000 (b mod d) / d), saturated.
-  const uint64_t q1 = b / d, r1 = b % d;
-  if (q1 > ~0ull / 8000ull) return ~0ull;
-  const uint64_t hi = q1 * 8000ull;
-  const uint64_t lo = (r1 * 8000ull) / d;  // r1 * 8000 < 2^45
-  const uint64_t s = hi + lo;
-  return s < hi ? ~0ull : s;
-}
-
-__device__ __forceinline__ uint64_t rate_bps(uint64_t b, uint32_t d) {
-  if (b <= kFastBytesMax) {
-    const uint64_t num = b * 8000ull;  // < 2^53: exact as a double
-    // The correctly rounded quotient is within one of floor(num/d) and never
-    // below it; one integer check removes the rounding step up.
-    uint64_t q = (uint64_t)((double)num / (double)d);
-    const uint64_t prod = q * (uint64_t)d;
-    if (prod > num) q -= 1;
-    else if (num - prod >= d) q += 1;
-    return q;
-  }
-  return rate_bps_wide(b, d);
-}
-
 __device__ __forceinline__ uint32_t ldg_nt(const uint32_t *p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ uint64_t ldg_nt(const uint64_t *p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ u32x4 ldg_nt4(const uint32_t *p) { return __builtin_nontemporal_load((const u32x4 *)p); }
@@ -333,8 +308,9 @@ struct Lds {
   uint32_t hslots;  // histogram cache slots (0 = none)
   uint32_t *hcur;   // per-host staging: entries this workgroup has staged
   HostEntry *se;    // per-host staging: this workgroup's range
-  uint32_t *tcur;   // spilled rows: partial rows this workgroup has staged
+  uint32_t *tcur;   // spilled rows: appends to each part of this workgroup's range
   TableEntry *te;   // spilled rows: this workgroup's range (NULL: misses and flushes use device atomics)
+  uint32_t tcap;    // spilled rows: entries in a part
   uint32_t *kcur;   // staged histogram keys: keys this workgroup has staged (without per-host staging)
   uint32_t *ke;     // staged histogram keys: this workgroup's range (NULL: the histogram cache)
   uint32_t *kp;     // staged histogram keys per partition (NULL: counted by the histogram kernels)
@@ -352,6 +328,24 @@ constexpr uint32_t kInSlot = 0x80000000u;
 // high half of hash * sets.
 __device__ __forceinline__ uint32_t cache_set(uint32_t row, uint32_t sets) {
   return __umulhi(row * 0x9E3779B1u, sets);
+}
+
+// Flows, bytes, packets and duration added to row `row` of the device table.
+__device__ __forceinline__ void add_device(u64 *g, uint32_t row, u64 flows, u64 b, u64 pk, u64 dur) {
+  u64 *o = g + (uint64_t)row * 8u;
+  atomicAdd(&o[0], flows);
+  atomicAdd(&o[1], b);
+  atomicAdd(&o[2], pk);
+  atomicAdd(&o[3], dur);
+}
+
+// Bulk flows and their rate sum, minimum and maximum.
+__device__ __forceinline__ void add_device_rate(u64 *g, uint32_t row, u64 nb, u64 sum, u64 mn, u64 mx) {
+  u64 *o = g + (uint64_t)row * 8u;
+  atomicAdd(&o[4], nb);
+  atomicAdd(&o[5], sum);
+  atomicMin(&o[6], mn);
+  atomicMax(&o[7], mx);
 }
 
 // Fields every record updates (the bulk count rides in the packed `cnt`).
@@ -398,12 +392,8 @@ __device__ __forceinline__ uint32_t accumulate(const Lds &L, u64 *g_row, uint32_
     atomicAdd(&t[kDur], (u64)dur);
     return kInSlot | slot;
   }
-  if (L.te) return row;  // spilled: the caller stages the record as a partial row
-  u64 *g = g_row + (uint64_t)row * 8u;
-  atomicAdd(&g[0], 1ull);
-  atomicAdd(&g[1], (u64)b);
-  atomicAdd(&g[2], (u64)pk);
-  atomicAdd(&g[3], (u64)dur);
+  if (L.te) return row;  // spilled: the caller stages the record
+  add_device(g_row, row, 1ull, b, pk, dur);
   return row;
 }
 
@@ -416,11 +406,7 @@ __device__ __forceinline__ void add_rate(const Lds &L, u64 *g_row, uint32_t code
     atomicMin(&t[kRateMin], (u64)rate);
     atomicMax(&t[kRateMax], (u64)rate);
   } else {
-    u64 *g = g_row + (uint64_t)code * 8u;
-    atomicAdd(&g[4], 1ull);
-    atomicAdd(&g[5], (u64)rate);
-    atomicMin(&g[6], (u64)rate);
-    atomicMax(&g[7], (u64)rate);
+    add_device_rate(g_row, code, 1ull, rate, rate, rate);
   }
 }
 
@@ -494,80 +480,54 @@ __device__ __forceinline__ void flush_hist(const Lds &L, uint32_t *h) {
   __syncthreads();
 }
 
-// One staged 32-byte entry of window L.win (two 16-byte stores).
-__device__ __forceinline__ void stage_entry(const Lds &L, uint32_t pos, uint32_t w, uint32_t row_kind, u64 x, u64 y,
-                                            u64 z) {
-  typedef u64 u64x2_ __attribute__((ext_vector_type(2)));
-  u64x2_ *e = (u64x2_ *)(L.te + pos);
-  e[0] = u64x2_{(u64)w | ((u64)row_kind << 32), x};
-  e[1] = u64x2_{y, z};
+// Place of k entries in the part of row's tile (beyond L.tcap: no room; a full
+// part's cursor is left alone, so that it cannot wrap).
+__device__ __forceinline__ uint32_t append_rows(const Lds &L, uint32_t row, uint32_t k) {
+  uint32_t *cur = &L.tcur[row / kTableTileRows];
+  return *(volatile uint32_t *)cur < L.tcap ? atomicAdd(cur, k) : L.tcap;
 }
 
-// Entries reserved for the wave's lanes with `want`: the first entry of the
-// wave's run (one LDS atomic by the first active lane); bal = the lanes.
-__device__ __forceinline__ uint32_t reserve_rows(uint32_t *cursor, bool want, uint64_t &bal, uint32_t per = 1u) {
-  bal = __builtin_amdgcn_ballot_w64(want);
-  if (!bal) return 0u;
-  uint32_t base = 0;
-  if (__lane_id() == (uint32_t)__builtin_ctzll(__builtin_amdgcn_read_exec()))
-    base = atomicAdd(cursor, per * (uint32_t)__builtin_popcountll(bal));
-  return __builtin_amdgcn_readfirstlane(base);
+// One staged entry of window L.win at place `pos` of its part.
+__device__ __forceinline__ void stage_entry(const Lds &L, uint32_t row, uint32_t pos, uint32_t kind, u64 x, u64 bytes) {
+  typedef u64 u64x2_ __attribute__((ext_vector_type(2)));
+  const uint32_t head =
+      (L.win << (kEntWindowShift - 32u)) | (kind << (kEntKindShift - 32u)) | ((row % kTableTileRows) << (kEntRowShift - 32u));
+  *(u64x2_ *)(L.te + (uint64_t)(row / kTableTileRows) * L.tcap + pos) = u64x2_{x, bytes | ((u64)head << 32)};
 }
 
 // Flush the LDS cache slots into window table g with device-scope atomics,
-// or, when the table spills and the workgroup's range has room for three
-// entries per claimed slot below `room`, stage them; then free them.
-__device__ __forceinline__ void flush_cache(const Lds &L, u64 *__restrict__ g, uint32_t room) {
+// or, when the table spills and the row's part has room, as staged entries;
+// then free them.
+__device__ __forceinline__ void flush_cache(const Lds &L, u64 *__restrict__ g) {
   __syncthreads();
-  bool stage = false;
-  if (L.te) {
-    // claimed slots, counted by every wave into the spare LDS counter word
-    uint32_t *claimed = L.tcur + 1;
-    if (threadIdx.x == 0) *claimed = 0u;
-    __syncthreads();
-    uint32_t c = 0;
-    for (uint32_t sl = threadIdx.x; sl < L.slots; sl += kThreads) c += L.tags[sl] != 0u;
-    for (uint32_t o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
-    if (__lane_id() == 0 && c) atomicAdd(claimed, c);
-    __syncthreads();
-    stage = *L.tcur + 3u * *claimed <= room;
-  }
-  if (stage) {
-    const uint64_t below = (1ull << __lane_id()) - 1ull;
-    for (uint32_t s0 = 0; s0 < L.slots; s0 += kThreads) {  // whole waves, so the reservation is uniform
-      const uint32_t sl = s0 + threadIdx.x;
-      const uint32_t tag = sl < L.slots ? L.tags[sl] : 0u;
-      uint64_t bal;
-      const uint32_t base = reserve_rows(L.tcur, tag != 0u, bal, 3u);
-      if (tag == 0u) continue;
-      u64 *t = L.acc + sl * kAccFields;
-      const uint32_t pos = base + 3u * (uint32_t)__builtin_popcountll(bal & below), row = tag - 1u;
-      stage_entry(L, pos, L.win, row | (kRowA << kRowKindShift), t[kCnt], t[kBytes], t[kPackets]);
-      stage_entry(L, pos + 1u, L.win, row | (kRowB << kRowKindShift), t[kDur], t[kRateSum], t[kRateMin]);
-      stage_entry(L, pos + 2u, L.win, row | (kRowC << kRowKindShift), t[kRateMax], 0ull, 0ull);
-      t[kCnt] = t[kBytes] = t[kPackets] = t[kDur] = t[kRateSum] = t[kRateMax] = 0;
-      t[kRateMin] = ~0ull;
-      L.tags[sl] = 0u;
-    }
-    __syncthreads();
-    return;
-  }
   for (uint32_t sl = threadIdx.x; sl < L.slots; sl += kThreads) {
     const uint32_t tag = L.tags[sl];
     if (tag == 0u) continue;
     u64 *t = L.acc + sl * kAccFields;
-    u64 *o = g + (uint64_t)(tag - 1u) * 8u;
-    const u64 cnt = t[kCnt];
-    atomicAdd(&o[0], cnt & 0xFFFFFFFFull);
-    atomicAdd(&o[1], t[kBytes]);
-    atomicAdd(&o[2], t[kPackets]);
-    atomicAdd(&o[3], t[kDur]);
-    const u64 nb = cnt >> 32;
-    if (nb) {
-      atomicAdd(&o[4], nb);
-      atomicAdd(&o[5], t[kRateSum]);
-      atomicMin(&o[6], t[kRateMin]);
-      atomicMax(&o[7], t[kRateMax]);
+    const uint32_t row = tag - 1u;
+    const u64 cnt = t[kCnt], nb = cnt >> 32;
+    bool staged = false;
+    if (L.te) {
+      const uint32_t k = nb ? 7u : 4u, pos = append_rows(L, row, k);
+      staged = pos + k <= L.tcap;
+      if (staged) {
+        stage_entry(L, row, pos, kRowCnt, cnt, 0ull);
+        stage_entry(L, row, pos + 1u, kRowBytes, t[kBytes], 0ull);
+        stage_entry(L, row, pos + 2u, kRowPackets, t[kPackets], 0ull);
+        stage_entry(L, row, pos + 3u, kRowDur, t[kDur], 0ull);
+        if (nb) {
+          stage_entry(L, row, pos + 4u, kRowRateSum, t[kRateSum], 0ull);
+          stage_entry(L, row, pos + 5u, kRowRateMin, t[kRateMin], 0ull);
+          stage_entry(L, row, pos + 6u, kRowRateMax, t[kRateMax], 0ull);
+        }
+      } else {
+        // the last places of a full part: entries that add nothing
+        for (uint32_t p = pos; p < L.tcap; ++p) stage_entry(L, row, p, kRowRateMax, 0ull, 0ull);
+      }
+    }
+    if (!staged) {
+      add_device(g, row, cnt & 0xFFFFFFFFull, t[kBytes], t[kPackets], t[kDur]);
+      if (nb) add_device_rate(g, row, nb, t[kRateSum], t[kRateMin], t[kRateMax]);
     }
     t[kCnt] = t[kBytes] = t[kPackets] = t[kDur] = t[kRateSum] = t[kRateMax] = 0;
     t[kRateMin] = ~0ull;
@@ -789,19 +749,21 @@ __device__ __forceinline__ void aggregate_tile(const Addr<R> &t, const uint32_t 
     // (a spare LDS row for invalid records instead of this branch measured
     // 10 % slower on the 64-site registry)
     if (valid[k]) code = accumulate<ACC_LDS>(L, g_tab, row[k], r.b[k], r.pk[k], dur, bulk);
-    // a spilled table: a record that missed the cache becomes a partial row
-    const bool spill = !ACC_LDS && L.te != nullptr;
-    const bool miss = spill && valid[k] && !(code & kInSlot);
-    uint64_t sbal = 0;
-    uint32_t sbase = 0;
-    if (spill) sbase = reserve_rows(L.tcur, miss, sbal);
+    // a spilled table: a record that missed the cache is staged, or added to
+    // the device table where its part is full
+    bool staged = false;
+    if (!ACC_LDS && L.te != nullptr) {
+      if (valid[k] && !(code & kInSlot)) {
+        const uint32_t pos = (r.b[k] >> kEntBytesBits) == 0u ? append_rows(L, row[k], 1u) : L.tcap;
+        staged = pos < L.tcap;
+        if (staged) stage_entry(L, row[k], pos, kRec, (u64)r.pk[k] | ((u64)dur << 32), r.b[k]);
+        else add_device(g_tab, row[k], 1ull, r.b[k], r.pk[k], dur);
+      }
+    }
     uint64_t rate = 0;
     if (bulk) rate = rate_bps(r.b[k], dur);
-    if (miss)
-      stage_entry(L, sbase + (uint32_t)__builtin_popcountll(sbal & below), L.win | (bulk ? kRecBulk : 0u),
-                  row[k] | (kRec << kRowKindShift), (u64)r.pk[k] | ((u64)dur << 32), r.b[k], rate);
     if (bulk) {
-      if (!miss) add_rate<ACC_LDS>(L, g_tab, code, rate);
+      if (!staged) add_rate<ACC_LDS>(L, g_tab, code, rate);
       // count in the row's histogram: registered sites only
       if ((FEAT & kFeatHist) && row[k] < a.hist_rows) {
         if (kst) {
@@ -899,10 +861,12 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const ClassifyArgs a
   constexpr bool HOSTS = (FEAT & kFeatHosts) != 0;
   const bool spill = !ACC_LDS && a.ts_entry != nullptr;
   const bool kst = HIST && a.ks_key != nullptr;
-  // cursors: per-host entries, spilled rows, the spilled-row flush's claimed
-  // slots, histogram keys
-  uint32_t *s_hcur = (uint32_t *)(lds + a.lds_off_ctr), *s_tcur = s_hcur + 1, *s_kcur = s_hcur + 3;
-  if ((HOSTS || spill || kst) && tid < 4u) s_hcur[tid] = 0u;
+  // cursors: per-host entries, histogram keys; the parts of spilled rows
+  uint32_t *s_hcur = (uint32_t *)(lds + a.lds_off_ctr), *s_kcur = s_hcur + 1;
+  if ((HOSTS || kst) && tid < 2u) s_hcur[tid] = 0u;
+  uint32_t *s_tcur = (uint32_t *)(lds + a.lds_off_tc);
+  if (spill)
+    for (uint32_t i = tid; i < a.ts_tiles; i += kThreads) s_tcur[i] = 0u;
   uint32_t *s_kp = (uint32_t *)(lds + a.lds_off_kp);
   const bool kcount = kst && a.kp_hist != nullptr;
   if (kcount) {
@@ -921,11 +885,11 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const ClassifyArgs a
   const uint64_t lo = (uint64_t)blockIdx.x * a.n / gridDim.x;
   const uint64_t hi = (uint64_t)(blockIdx.x + 1) * a.n / gridDim.x;
   Lds L{s_root, s_lines, s_acc, s_tags, slots, s_htags, s_htags + hslots, hslots, s_hcur,
-        HOSTS ? a.hs_entry + lo : nullptr, s_tcur, spill ? a.ts_entry + lo + (uint64_t)blockIdx.x * a.ts_extra : nullptr,
+        HOSTS ? a.hs_entry + lo : nullptr, s_tcur,
+        spill ? (TableEntry *)(a.ts_entry + kTableRangeBytes * (lo + (uint64_t)blockIdx.x * a.ts_extra)) : nullptr,
+        spill ? table_part_cap(hi - lo, a.ts_extra, a.ts_tiles) : 0u,
         s_kcur, kst ? a.ks_key + lo : nullptr, kcount ? s_kp : nullptr, a.kp_shift, hcount ? s_hp : nullptr, a.hp_bits,
         0u, 0u};
-  // spilled rows: the entries this workgroup's range holds
-  const uint32_t t_cap = (uint32_t)(hi - lo) + a.ts_extra;
   if (lo == hi) {
     // empty slice: leave an empty table whose window keeps the slots ordered
     if (ACC_LDS && a.ws) {
@@ -933,7 +897,8 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const ClassifyArgs a
       flush_partial(a, s_acc, window_of(a, lo ? lo - 1 : 0, we));
     }
     if (HOSTS && tid == 0) a.hs_count[blockIdx.x] = 0u;
-    if (spill && tid == 0) a.ts_count[blockIdx.x] = 0u;
+    if (spill)
+      for (uint32_t j = tid; j < a.ts_tiles; j += kThreads) a.ts_count[(uint64_t)blockIdx.x * a.ts_tiles + j] = 0u;
     if (kst && tid == 0) a.ks_count[blockIdx.x] = 0u;
     if (kcount)
       for (uint32_t j = tid; j < a.kp_parts; j += kThreads) a.kp_hist[(uint64_t)blockIdx.x * a.kp_parts + j] = 0u;
@@ -972,9 +937,9 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const ClassifyArgs a
       if (seg_end >= hi && a.ws) flush_partial(a, s_acc, w);
       else flush_atomic(s_acc, g_tab, rows);
     } else if (slots) {
-      // room for this flush: what the range holds less one entry for each
-      // record still to come
-      flush_cache(L, g_tab, t_cap - (uint32_t)(hi - seg_end));
+      flush_cache(L, g_tab);
+    } else if (spill) {
+      __syncthreads();  // a part's entries are in window order
     }
     if (HIST && hslots) flush_hist(L, h_tab);
     i = seg_end;
@@ -982,7 +947,9 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const ClassifyArgs a
   if (HOSTS || spill || kst) {
     __syncthreads();
     if (HOSTS && tid == 0) a.hs_count[blockIdx.x] = *s_hcur;
-    if (spill && tid == 0) a.ts_count[blockIdx.x] = *s_tcur;
+    if (spill)
+      for (uint32_t j = tid; j < a.ts_tiles; j += kThreads)
+        a.ts_count[(uint64_t)blockIdx.x * a.ts_tiles + j] = s_tcur[j] < L.tcap ? s_tcur[j] : L.tcap;
     // with per-host staging the keys share its cursor
     if (kst && tid == 0) a.ks_count[blockIdx.x] = HOSTS ? *s_hcur : *s_kcur;
     if (kcount)
@@ -1530,14 +1497,33 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
   // a table beyond LDS with a workspace that holds its spilled rows: the
   // misses of the row cache and its flushes are staged and merged by the
   // table kernels instead of device-scope atomics
-  const bool spill = !reg->acc_in_lds && rec->n > 0 && rec->n < (1ull << 32) && p.workspace &&
-                     ((uintptr_t)p.workspace & 255u) == 0 && table_fits(n_windows, (uint32_t)rows) &&
-                     p.workspace_bytes >= table_spill_bytes(rec->n, grid, n_windows, (uint32_t)rows, reg->cache_slots);
+  // (whose parts' LDS cursors come out of the cache's slots where the plan
+  // leaves no room beside them)
+  uint32_t lds_launch = reg->lds_bytes;
+  const uint32_t lds_budget = (reg->lds_bytes <= kLdsMax / 2 ? kLdsMax / 2 : kLdsMax) - kLdsReserve;
+  bool spill = !reg->acc_in_lds && rec->n > 0 && rec->n < (1ull << 32) && p.workspace &&
+               ((uintptr_t)p.workspace & 255u) == 0 && table_fits(n_windows, (uint32_t)rows) &&
+               p.workspace_bytes >= table_spill_bytes(rec->n, grid, n_windows, (uint32_t)rows, reg->cache_slots);
   if (spill) {
-    const TableStage ts = table_stage(p.workspace, rec->n, grid, n_windows, (uint32_t)rows, reg->cache_slots);
+    const uint32_t tiles = table_tiles((uint32_t)rows), need = 4u * tiles;
+    constexpr uint32_t kSlotBytes = 8u * kAccFields + 4u;
+    const uint32_t end = (lds_launch + 15u) & ~15u, cache = reg->cache_slots * kSlotBytes;
+    if (end + need <= lds_budget) {
+      a.lds_off_tc = end;
+      lds_launch = end + need;
+    } else if (cache >= need + 16u) {
+      a.cache_slots = ((cache - need - 16u) / kSlotBytes) & ~3u;
+      a.lds_off_tc = (reg->lds_off_acc + a.cache_slots * kSlotBytes + 15u) & ~15u;
+    } else {
+      spill = false;
+    }
+  }
+  if (spill) {
+    const TableStage ts = table_stage(p.workspace, rec->n, grid, (uint32_t)rows, reg->cache_slots);
     a.ts_entry = ts.entry;
     a.ts_count = ts.count;
     a.ts_extra = (uint32_t)table_extra(reg->cache_slots);
+    a.ts_tiles = table_tiles((uint32_t)rows);
   }
   // histograms with a workspace that also holds their keys, after what the
   // tables use of it: staged keys and the histogram kernels instead of the
@@ -1556,12 +1542,10 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
       a.ks_count = ks.count;
     }
   }
-  uint32_t lds_launch = reg->lds_bytes;
   if (p.rate_hist && !hist_work) {
     // the histogram cache takes the LDS the registry leaves free, within the
     // budget that keeps the registry's workgroups per CU
-    const uint32_t off = (reg->lds_bytes + 15u) & ~15u;
-    const uint32_t budget = (reg->lds_bytes <= kLdsMax / 2 ? kLdsMax / 2 : kLdsMax) - kLdsReserve;
+    const uint32_t off = (lds_launch + 15u) & ~15u, budget = lds_budget;
     uint32_t hs = budget > off ? (budget - off) / 8u : 0u;
     hs = (hs < kHistSlotsMax ? hs : kHistSlotsMax) & ~3u;
     if (hs < 64u) hs = 0;
@@ -1573,7 +1557,7 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
     // the keys' partition counts in LDS too, when they fit that budget
     // (otherwise the count kernel counts them)
     const uint32_t off = (lds_launch + 15u) & ~15u;
-    const uint32_t budget = (reg->lds_bytes <= kLdsMax / 2 ? kLdsMax / 2 : kLdsMax) - kLdsReserve;
+    const uint32_t budget = lds_budget;
     if (off + 4u * ks.nparts <= budget) {
       a.kp_hist = ks.phist;
       a.kp_over = ks.over;
@@ -1588,7 +1572,7 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
     // (otherwise the count kernel counts them)
     const HostStage st = host_stage(ht->work, rec->n, grid);
     const uint32_t off = (lds_launch + 15u) & ~15u;
-    const uint32_t budget = (reg->lds_bytes <= kLdsMax / 2 ? kLdsMax / 2 : kLdsMax) - kLdsReserve;
+    const uint32_t budget = lds_budget;
     if (rec->n > 0 && off + (4u << st.pbits) <= budget) {
       a.hp_hist = st.phist;
       a.hp_bits = st.pbits;
@@ -1597,7 +1581,7 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
       lds_launch = off + (4u << st.pbits);
     }
   }
-  if (ht || spill || hist_work) {
+  if (ht || hist_work) {
     // the staging cursors: words in the bytes every LDS plan leaves free
     a.lds_off_ctr = (lds_launch + 15u) & ~15u;
     lds_launch = a.lds_off_ctr + 16u;
@@ -1667,8 +1651,9 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
   if (e != hipSuccess) return hip_fail(e, "classify launch");
   if (spill) {
     const TableFlags tf{fl.flags, fl.threshold, fl.need, fl.n_sites};
-    const int rc = table_merge_launch(p.workspace, rec->n, grid, n_windows, (uint32_t)rows, reg->cache_slots,
-                                      (unsigned long long *)acc, tf, stream);
+    const BulkRule bulk{p.bulk_bytes, p.min_avg_packet_bytes, p.min_packets, p.min_duration_ms};
+    const int rc = table_merge_launch(p.workspace, rec->n, grid, window_offsets, n_windows, (uint32_t)rows,
+                                      reg->cache_slots, bulk, (unsigned long long *)acc, tf, stream);
     if (rc != GNM_OK) return rc;
   } else if (use_ws) {
     // waves per reduce workgroup: enough for one round of kRedUnroll loads per
