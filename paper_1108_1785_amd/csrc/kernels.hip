@@ -71,6 +71,11 @@ static_assert((1u << kHistKeyBits) > kBuckets, "bucket must fit the key's low bi
 constexpr uint32_t kMedFullBatches = kBuckets / kMedBatchWords;  // batches with no bucket past the row
 static_assert(kMedBatches <= 64, "batch sums are held one per lane");
 
+// Trie layouts a classify kernel is built for: leaf lines in LDS and nothing
+// else below the root; nodes (and any leaf lines in LDS); leaf lines (and
+// nodes) in device memory.
+enum Layout : int { kLinesOnly = 0, kNodes = 1, kLinesGlobal = 2 };
+
 struct LocalRanges {
   uint32_t n;
   uint32_t lo[kMaxLocalRanges];
@@ -136,7 +141,7 @@ __device__ __forceinline__ bool in_ranges(const LocalRanges &L, uint32_t ip) {
 // costs one 16-byte read and usually resolves the address; a leaf line costs
 // one 64-byte line read (keys) and one read of the same line (site).  Lanes
 // with nothing to resolve read the dummy entry 0 rather than branching.
-template <int R, bool LINES_LDS>
+template <int R, int LAY>
 __device__ __forceinline__ void lookup_sites(const uint32_t (&ip)[R], const uint32_t (&root_e)[R],
                                              const bool (&act)[R], uint32_t (&site)[R], gu32 *wide,
                                              const uint32_t *s_lines, gu32 *g_lines, uint32_t root_bits,
@@ -158,7 +163,7 @@ __device__ __forceinline__ void lookup_sites(const uint32_t (&ip)[R], const uint
   }
   // wide nodes: first level node_bits (>= 4) wide, then 8 bits, so at most
   // 1 + ceil(20 / 8) = 4 levels below a root of >= 8 bits
-  for (int depth = 0; depth < 4 && __builtin_amdgcn_ballot_w64(any); ++depth) {
+  for (int depth = 0; LAY != kLinesOnly && depth < 4 && __builtin_amdgcn_ballot_w64(any); ++depth) {
     const uint32_t smax = depth == 0 ? node_bits : kNodeStrideMax;
     const uint32_t ns = shift > smax ? shift - smax : 0u;
     const uint32_t mask = (1u << (shift - ns)) - 1u;
@@ -206,7 +211,7 @@ __device__ __forceinline__ void lookup_sites(const uint32_t (&ip)[R], const uint
     }
   }
   // leaf lines: position = number of starts 1..7 that are <= ip
-  if (LINES_LDS) {
+  if (LAY != kLinesGlobal) {
     // LDS: the keys, then the one site code at the position
     if (!__builtin_amdgcn_ballot_w64(any_line)) return;
     u32x4 k0[R], k1[R];
@@ -589,14 +594,29 @@ __device__ __forceinline__ void load_addr(Addr<R> &t, const ClassifyArgs &a, uin
   }
 }
 
-template <int R, bool VEC>
+// The byte counts of 4 records take two loads of the same lines.  With the
+// non-temporal hint the first load's lines may go before the second reads
+// them: where lookups read trie nodes, whose misses take the same cache
+// request slots, that costs 2 to 6 % (7.5 M cache line requests of a 10
+// M-record launch on the 1,000-site registry against 6.7 M without the hint;
+// 102.0 against 95.6 us a call, 639 against 625 for 8 windows in one).  Without
+// nodes the hint is up to 1 % faster (256 windows on the 64-site registry,
+// 1,367 against 1,386 us).
+template <int R, bool VEC, int LAY>
 __device__ __forceinline__ void load_rest(Rest<R> &t, const ClassifyArgs &a, uint64_t base, uint64_t end) {
   // (lanes past the end load the range's last records, as in load_addr)
   if (VEC) {
     const uint64_t idx = base + 4ull * threadIdx.x;
     const uint64_t at = idx < end ? idx : end - 4;
     const u32x4 pk = ldg_nt4(a.packets + at), f = ldg_nt4(a.first + at), l = ldg_nt4(a.last + at);
-    const u64x2 b0 = ldg_nt2(a.bytes + at), b1 = ldg_nt2(a.bytes + at + 2);
+    u64x2 b0, b1;
+    if (LAY != kLinesOnly) {
+      b0 = *(const u64x2 *)(a.bytes + at);
+      b1 = *(const u64x2 *)(a.bytes + at + 2);
+    } else {
+      b0 = ldg_nt2(a.bytes + at);
+      b1 = ldg_nt2(a.bytes + at + 2);
+    }
     t.pk[0] = pk.x; t.pk[1] = pk.y; t.pk[2] = pk.z; t.pk[3] = pk.w;
     t.f[0] = f.x; t.f[1] = f.y; t.f[2] = f.z; t.f[3] = f.w;
     t.l[0] = l.x; t.l[1] = l.y; t.l[2] = l.z; t.l[3] = l.w;
@@ -638,7 +658,7 @@ __device__ __forceinline__ void load_single(Addr<R> &t, Rest<R> &r, const Classi
 
 // Classify the tile's records from their addresses: the accumulator row of
 // each (2 * site + direction, or the NODIR row).
-template <int R, bool LINES_LDS>
+template <int R, int LAY>
 __device__ __forceinline__ void classify_tile(const Addr<R> &t, const ClassifyArgs &a, const Lds &L,
                                               uint32_t (&row)[R]) {
   const uint32_t rows = a.rows;
@@ -672,7 +692,7 @@ __device__ __forceinline__ void classify_tile(const Addr<R> &t, const ClassifyAr
     inbound[k] = ld[k];
     remote[k] = ld[k] ? t.s[k] : t.d[k];
   }
-  lookup_sites<R, LINES_LDS>(remote, re, one, site, a.wide, L.lines, a.lines, a.root_bits, a.node_bits);
+  lookup_sites<R, LAY>(remote, re, one, site, a.wide, L.lines, a.lines, a.root_bits, a.node_bits);
 #pragma unroll
   for (int k = 0; k < R; ++k) row[k] = one[k] ? 2u * site[k] + (inbound[k] ? 0u : 1u) : rows - 1u;
 }
@@ -783,11 +803,11 @@ __device__ __forceinline__ void aggregate_tile(const Addr<R> &t, const uint32_t 
   }
 }
 
-template <int R, bool LINES_LDS, bool ACC_LDS, uint32_t FEAT>
+template <int R, int LAY, bool ACC_LDS, uint32_t FEAT>
 __device__ __forceinline__ void process_tile(const Addr<R> &t, const Rest<R> &r, const ClassifyArgs &a,
                                              const Lds &L, u64 *g_tab, uint32_t *h_tab) {
   uint32_t row[R];
-  classify_tile<R, LINES_LDS>(t, a, L, row);
+  classify_tile<R, LAY>(t, a, L, row);
   aggregate_tile<R, ACC_LDS, FEAT>(t, row, r, a, L, g_tab, h_tab);
 }
 
@@ -796,7 +816,7 @@ __device__ __forceinline__ void process_tile(const Addr<R> &t, const Rest<R> &r,
 // overlaps the locality tests and the trie walk.  (Measured: prefetching the
 // other fields a tile ahead as well, or in the middle of the walk, gained
 // nothing at 4 waves per SIMD.)
-template <int R, bool VEC, bool LINES_LDS, bool ACC_LDS, uint32_t FEAT>
+template <int R, bool VEC, int LAY, bool ACC_LDS, uint32_t FEAT>
 __device__ __forceinline__ void process_range(const ClassifyArgs &a, const Lds &L, u64 *g_tab, uint32_t *h_tab,
                                               uint64_t lo, uint64_t hi) {
   constexpr uint64_t T = (uint64_t)kThreads * R;
@@ -804,11 +824,11 @@ __device__ __forceinline__ void process_range(const ClassifyArgs &a, const Lds &
   load_addr<R, VEC>(cur, a, lo, hi);
   for (uint64_t base = lo; base < hi; base += T) {
     Rest<R> rest;
-    load_rest<R, VEC>(rest, a, base, hi);
+    load_rest<R, VEC, LAY>(rest, a, base, hi);
     Addr<R> nxt;
     load_addr<R, VEC>(nxt, a, base + T, hi);  // past the end: reloads the last records, marked invalid
     uint32_t row[R];
-    classify_tile<R, LINES_LDS>(cur, a, L, row);
+    classify_tile<R, LAY>(cur, a, L, row);
     aggregate_tile<R, ACC_LDS, FEAT>(cur, row, rest, a, L, g_tab, h_tab);
     cur = nxt;
   }
@@ -834,7 +854,7 @@ __global__ void zero_words_kernel(uint32_t *__restrict__ p, uint64_t n) {
   }
 }
 
-template <int R, bool VEC, bool LINES_LDS, bool ACC_LDS, uint32_t FEAT>
+template <int R, bool VEC, int LAY, bool ACC_LDS, uint32_t FEAT>
 __global__ __launch_bounds__(kThreads) void classify_kernel(const ClassifyArgs a) {
   constexpr bool HIST = (FEAT & kFeatHist) != 0;
   extern __shared__ __align__(16) unsigned char lds[];
@@ -847,7 +867,7 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const ClassifyArgs a
   // stage the trie root (with locality masks) and, when they fit, the leaf lines
   const uint32_t nroot = 1u << a.root_bits;
   for (uint32_t i = tid; i < nroot; i += kThreads) s_root[i] = a.root[i];
-  if (LINES_LDS)
+  if (LAY != kLinesGlobal)
     for (uint32_t i = tid; i < a.n_line_words; i += kThreads) s_lines[i] = a.lines[i];
   // the table, or the cache slots' rows and their tags
   const uint32_t slots = ACC_LDS ? 0u : a.cache_slots;
@@ -927,11 +947,11 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const ClassifyArgs a
         Rest<R> mr;
         const bool head = tid < a0 - i, tail = tid >= 3 && tid - 3 < seg_end - a1;
         load_single(m, mr, a, head ? i + tid : a1 + (tid - 3), head || tail);
-        process_tile<R, LINES_LDS, ACC_LDS, FEAT>(m, mr, a, L, g_tab, h_tab);
+        process_tile<R, LAY, ACC_LDS, FEAT>(m, mr, a, L, g_tab, h_tab);
       }
-      if (a0 < a1) process_range<4, true, LINES_LDS, ACC_LDS, FEAT>(a, L, g_tab, h_tab, a0, a1);
+      if (a0 < a1) process_range<4, true, LAY, ACC_LDS, FEAT>(a, L, g_tab, h_tab, a0, a1);
     } else {
-      process_range<R, false, LINES_LDS, ACC_LDS, FEAT>(a, L, g_tab, h_tab, i, seg_end);
+      process_range<R, false, LAY, ACC_LDS, FEAT>(a, L, g_tab, h_tab, i, seg_end);
     }
     if (ACC_LDS) {
       if (seg_end >= hi && a.ws) flush_partial(a, s_acc, w);
@@ -1300,36 +1320,43 @@ int device_cus(int dev) {
 
 typedef void (*KernelFn)(const ClassifyArgs);
 
-// variant slot: feat * 16 + shape * 4 + lists * 2 + acc; shapes: R=1, R=2, R=4 strided, R=4 vector
-template <int R, bool V, uint32_t F>
-KernelFn pick_la(bool lists, bool acc) {
-  if (lists) return acc ? classify_kernel<R, V, true, true, F> : classify_kernel<R, V, true, false, F>;
-  return acc ? classify_kernel<R, V, false, true, F> : classify_kernel<R, V, false, false, F>;
-}
+constexpr int kLayouts = 3, kShapes = 4, kVariants = 4 * kShapes * kLayouts * 2;
 
-template <uint32_t F>
-KernelFn pick_shape(int shape, bool lists, bool acc) {
-  switch (shape) {
-    case 0: return pick_la<1, false, F>(lists, acc);
-    case 1: return pick_la<2, false, F>(lists, acc);
-    case 2: return pick_la<4, false, F>(lists, acc);
-    default: return pick_la<4, true, F>(lists, acc);
+// variant slot: ((feat * kShapes + shape) * kLayouts + layout) * 2 + acc; shapes: R=1, R=2, R=4 strided, R=4 vector
+template <int R, bool V, uint32_t F>
+KernelFn pick_la(int layout, bool acc) {
+  switch (layout) {
+    case kLinesOnly:
+      return acc ? classify_kernel<R, V, kLinesOnly, true, F> : classify_kernel<R, V, kLinesOnly, false, F>;
+    case kNodes: return acc ? classify_kernel<R, V, kNodes, true, F> : classify_kernel<R, V, kNodes, false, F>;
+    default:
+      return acc ? classify_kernel<R, V, kLinesGlobal, true, F> : classify_kernel<R, V, kLinesGlobal, false, F>;
   }
 }
 
-KernelFn pick(int shape, bool lists, bool acc, uint32_t feat) {
+template <uint32_t F>
+KernelFn pick_shape(int shape, int layout, bool acc) {
+  switch (shape) {
+    case 0: return pick_la<1, false, F>(layout, acc);
+    case 1: return pick_la<2, false, F>(layout, acc);
+    case 2: return pick_la<4, false, F>(layout, acc);
+    default: return pick_la<4, true, F>(layout, acc);
+  }
+}
+
+KernelFn pick(int shape, int layout, bool acc, uint32_t feat) {
   switch (feat) {
-    case 0: return pick_shape<0>(shape, lists, acc);
-    case kFeatHist: return pick_shape<kFeatHist>(shape, lists, acc);
-    case kFeatHosts: return pick_shape<kFeatHosts>(shape, lists, acc);
-    default: return pick_shape<kFeatHist | kFeatHosts>(shape, lists, acc);
+    case 0: return pick_shape<0>(shape, layout, acc);
+    case kFeatHist: return pick_shape<kFeatHist>(shape, layout, acc);
+    case kFeatHosts: return pick_shape<kFeatHosts>(shape, layout, acc);
+    default: return pick_shape<kFeatHist | kFeatHosts>(shape, layout, acc);
   }
 }
 
 // Allow every kernel variant the full 160 KB of LDS, once per device.
 hipError_t allow_lds(KernelFn fn, int slot, int dev) {
   static std::mutex mu;
-  static bool done[64][64] = {};
+  static bool done[64][kVariants] = {};
   std::lock_guard<std::mutex> g(mu);
   if (dev >= 0 && dev < 64 && done[dev][slot]) return hipSuccess;
   hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
@@ -1600,9 +1627,10 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
                    aligned16(rec->packets) && aligned16(rec->first_ms) && aligned16(rec->last_ms);
   const int shape = vec ? 3 : (R == 1 ? 0 : (R == 2 ? 1 : 2));
   const uint32_t feat = (p.rate_hist ? kFeatHist : 0u) | (p.hosts ? kFeatHosts : 0u);
-  KernelFn fn = pick(shape, reg->lines_in_lds, reg->acc_in_lds, feat);
+  const int layout = !reg->lines_in_lds ? kLinesGlobal : (reg->info.n_nodes ? kNodes : kLinesOnly);
+  KernelFn fn = pick(shape, layout, reg->acc_in_lds, feat);
   if (rec->n > 0) {
-    e = allow_lds(fn, (int)feat * 16 + shape * 4 + (reg->lines_in_lds ? 2 : 0) + (reg->acc_in_lds ? 1 : 0), dev);
+    e = allow_lds(fn, (((int)feat * kShapes + shape) * kLayouts + layout) * 2 + (reg->acc_in_lds ? 1 : 0), dev);
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
   }
   if (hist_work) {
