@@ -14,6 +14,13 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr uint32_t kBuckets = 10001;  // rate histogram: 10 kbps buckets, the last for >= 100 Mbps
 constexpr uint32_t kBucketBps = 10000;
 
+// First record of classify workgroup b's slice of n records on `grid`
+// workgroups: an even split cut at multiples of 4 records (slice `grid`
+// starts at n, where the last one ends).
+__host__ __device__ inline uint64_t slice_lo(uint32_t b, uint64_t n, uint32_t grid) {
+  return b < grid ? ((uint64_t)b * n / grid) & ~3ull : n;
+}
+
 // Histogram bucket of a rate (§III.B.2, TransRate Kernel): floor(rate /
 // 10 kbps), every rate of 100 Mbps and above in the last bucket.
 __device__ __forceinline__ uint32_t rate_bucket(uint64_t rate) {

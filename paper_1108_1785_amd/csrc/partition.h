@@ -51,7 +51,7 @@ struct PartArgs {
 // First staged entry of classify workgroup b: its first record, plus the
 // extra room of the workgroups before it.
 __device__ __forceinline__ uint64_t part_stage_lo(uint32_t b, uint64_t n, uint32_t grid, uint64_t extra) {
-  return (uint64_t)b * n / grid + (uint64_t)b * extra;
+  return slice_lo(b, n, grid) + (uint64_t)b * extra;
 }
 
 // Partition counts of classify workgroup b's entries (dynamic LDS: nparts

@@ -88,14 +88,13 @@ __global__ __launch_bounds__(kTableThreads) void table_reduce_kernel(const Merge
     if (w > 0) wlo = q.woff[w] < q.n ? q.woff[w] : q.n;
     if (w + 1u < q.n_windows) whi = q.woff[w + 1u] < q.n ? q.woff[w + 1u] : q.n;
   }
-  // classify workgroups whose slices [b n / grid, (b + 1) n / grid) meet it, a
-  // wave for each; four entries per lane in flight
+  // classify workgroups whose slices meet it, a wave for each; four entries per lane in flight
   const uint32_t lane = threadIdx.x % 64u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);
   if (wlo < whi) {
     uint32_t b0 = (uint32_t)(wlo * q.grid / q.n);
     b0 = b0 ? b0 - 1u : 0u;
     for (uint32_t b = b0 + wave; b < q.grid; b += kTableThreads / 64u) {
-      const uint64_t lo = (uint64_t)b * q.n / q.grid, hi = (uint64_t)(b + 1u) * q.n / q.grid;
+      const uint64_t lo = slice_lo(b, q.n, q.grid), hi = slice_lo(b + 1u, q.n, q.grid);
       if (lo >= whi) break;
       if (hi <= wlo || lo == hi) continue;
       const uint32_t cap = table_part_cap(hi - lo, q.extra, q.tiles);
