@@ -465,9 +465,10 @@ uint64_t gnm_static_scratch_bytes(void);
  *                   threshold" when the threshold is a multiple of 10 kbps);
  *                   bit 2 + d = bit d is set in this window and in the one
  *                   before it (the warning).
- * Enqueues two kernels: the medians and low bits (one workgroup per
- * (window, site), reading each histogram once), then the two-window rule
- * (one lane per site).  Errors: GNM_E_INVAL (null pointers, n_windows = 0,
+ * Enqueues the median kernel (one workgroup per (window, site), reading
+ * each histogram once), which for one window also applies the two-window
+ * rule; for several, or when prev_flags lies in an array written here, a
+ * second kernel does (one lane per site).  Errors: GNM_E_INVAL (null pointers, n_windows = 0,
  * a registry of another device), GNM_E_UNSUPPORTED (host-only registry),
  * GNM_E_HIP.
  */

@@ -68,7 +68,7 @@ constexpr uint32_t kHistSlotsMax = 4096;  // LDS histogram cache slots (8 bytes 
 constexpr uint32_t kMedWaves = 4;         // median kernel: waves sharing one (window, site) item
 constexpr uint32_t kMedRun = 16;          // buckets per lane per batch: 64 * 16 = 1024 per batch
 constexpr uint32_t kMedBatchWords = 64u * kMedRun;
-constexpr uint32_t kMedBatches = (kBuckets + kMedBatchWords - 1u) / kMedBatchWords;  // 5
+constexpr uint32_t kMedBatches = (kBuckets + kMedBatchWords - 1u) / kMedBatchWords;  // 10
 static_assert((1u << kHistKeyBits) > kBuckets, "bucket must fit the key's low bits");
 constexpr uint32_t kMedFullBatches = kBuckets / kMedBatchWords;  // batches with no bucket past the row
 static_assert(kMedBatches <= 64, "batch sums are held one per lane");
@@ -1174,20 +1174,34 @@ __global__ void flag_kernel(const u64 *__restrict__ acc, uint32_t n_windows, uin
   flags[i] = f;
 }
 
-__device__ __forceinline__ u64 wave_sum(u64 x) {
-#pragma unroll
-  for (uint32_t o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+// x of the lane that the DPP control names (0 where it names none), on the
+// rows of 16 lanes in ROWS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ u64 dpp64(u64 x) {
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, ROWS, 0xF, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), CTRL, ROWS, 0xF, false);
+  return ((u64)hi << 32) | lo;
+}
+
+// Inclusive sums over the wave's lanes by register moves between lanes: row
+// shifts by 1, 2, 4, 8, then the last lane of row 0 (2) to row 1 (3) and of
+// row 1 to rows 2 and 3.  All lanes active.
+__device__ __forceinline__ u64 wave_inclusive_scan(u64 x) {
+  x += dpp64<0x111, 0xF>(x);
+  x += dpp64<0x112, 0xF>(x);
+  x += dpp64<0x114, 0xF>(x);
+  x += dpp64<0x118, 0xF>(x);
+  x += dpp64<0x142, 0xA>(x);
+  x += dpp64<0x143, 0xC>(x);
   return x;
 }
 
-__device__ __forceinline__ u64 wave_inclusive_scan(u64 x, uint32_t lane) {
-#pragma unroll
-  for (uint32_t o = 1; o < 64; o <<= 1) {
-    const u64 y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  return x;
+__device__ __forceinline__ u64 lane_u64(u64 x, uint32_t lane) {
+  return ((u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
 }
+
+__device__ __forceinline__ u64 wave_sum(u64 x) { return lane_u64(wave_inclusive_scan(x), 63u); }
 
 // Lower-median bucket of one histogram row: the bucket holding the
 // ceil(total/2)-th smallest count.  `bsum` holds, on lane b, the total of
@@ -1197,9 +1211,9 @@ __device__ __forceinline__ u64 wave_inclusive_scan(u64 x, uint32_t lane) {
 __device__ __forceinline__ uint32_t row_median(const uint32_t *row, u64 bsum, u64 total, uint32_t lane) {
   if (total == 0u) return 0xFFFFFFFFu;
   const u64 target = total - total / 2u;
-  const u64 incl = wave_inclusive_scan(bsum, lane);
+  const u64 incl = wave_inclusive_scan(bsum);
   const uint32_t b = (uint32_t)__ffsll((unsigned long long)__ballot(incl >= target)) - 1u;
-  const u64 before = __shfl(incl - bsum, b, 64);
+  const u64 before = lane_u64(incl - bsum, b);
   const uint32_t base = b * kMedBatchWords + lane * kMedRun;
   uint32_t v[kMedRun];
   u64 s = 0;
@@ -1208,7 +1222,7 @@ __device__ __forceinline__ uint32_t row_median(const uint32_t *row, u64 bsum, u6
     v[j] = base + j < kBuckets ? row[base + j] : 0u;
     s += v[j];
   }
-  const u64 li = wave_inclusive_scan(s, lane) + before;
+  const u64 li = wave_inclusive_scan(s) + before;
   const uint32_t owner = (uint32_t)__ffsll((unsigned long long)__ballot(li >= target)) - 1u;
   uint32_t m = 0;
   if (lane == owner) {
@@ -1219,7 +1233,7 @@ __device__ __forceinline__ uint32_t row_median(const uint32_t *row, u64 bsum, u6
       if (c >= target) { m = base + j; break; }
     }
   }
-  return __shfl(m, owner, 64);
+  return (uint32_t)__builtin_amdgcn_readlane((int)m, owner);
 }
 
 // This lane's part of the totals of batch b of two rows (buckets b*1024 +
@@ -1234,8 +1248,8 @@ __device__ __forceinline__ void batch_sums(const uint32_t *r0, const uint32_t *r
   uint32_t v0[kMedRun], v1[kMedRun];
 #pragma unroll
   for (uint32_t j = 0; j < kMedRun; ++j) {
-    v0[j] = __builtin_nontemporal_load(p0 + j * 64u);
-    v1[j] = __builtin_nontemporal_load(p1 + j * 64u);
+    v0[j] = p0[j * 64u];
+    v1[j] = p1[j * 64u];
   }
   s0 = 0;
   s1 = 0;
@@ -1247,27 +1261,34 @@ __device__ __forceinline__ void batch_sums(const uint32_t *r0, const uint32_t *r
   }
 }
 
-// Lower medians of the rate histograms: one workgroup of 4 waves per (window,
-// site) item.  The waves share the item's two rows (inbound, outbound): each
-// streams every 4th 1024-bucket batch of both rows once (32 loads in flight
-// per lane) and leaves the batch totals in LDS; then wave d walks row d from
-// those totals, re-reading only the batch that holds the median.  (One wave
-// per item left a single window's 1,000 items too few waves to cover the
-// memory latency.)  Writes the median buckets (NO_MEDIAN when a row has no
-// bulk flow) when `median` is not NULL, and bits 0/1 of the item's flag
-// byte: total >= need and bucket * 10 kbps < threshold.
-__global__ __launch_bounds__(64 * kMedWaves) void median_kernel(const uint32_t *__restrict__ hist, uint64_t items,
-                                                               uint64_t threshold, uint64_t need,
-                                                               uint32_t *__restrict__ median,
-                                                               uint8_t *__restrict__ flags) {
+// Lower medians of the rate histograms: one workgroup per (window, site)
+// item, of 4 waves, or one per batch when items are few (the launch decides).
+// The waves share the item's two rows (inbound, outbound): each streams every
+// 4th 1024-bucket batch of both rows once (32 loads in flight per lane) and
+// leaves the batch totals in LDS; then wave d walks row d from those totals,
+// re-reading only the batch that holds the median.  Writes the median buckets
+// (NO_MEDIAN when a row has no bulk flow) when `median` is not NULL, and bits
+// 0/1 of the item's flag byte: total >= need and bucket * 10 kbps <
+// threshold.  With `prev` (one window) also bits 2/3: bit d set here and in
+// the window before.
+// Bound by reading 80 KB per item, and for few items by its chain of loads
+// and sums over lanes.  1,000 items just filled (80 MB): 17.9 us (4.5 TB/s);
+// 22.6 with non-temporal loads, which fetch rows that the caches still hold
+// (16,000 items: 284 us, non-temporal 347).  Both rows kept in registers by
+// ten waves, nothing re-read: 26.5 (registers allow one workgroup per CU).
+__global__ __launch_bounds__(64 * kMedBatches) void median_kernel(const uint32_t *__restrict__ hist, uint64_t items,
+                                                                 uint64_t threshold, uint64_t need,
+                                                                 uint32_t *__restrict__ median,
+                                                                 uint8_t *__restrict__ flags,
+                                                                 const uint8_t *__restrict__ prev) {
   __shared__ u64 s_bsum[2][kMedBatches];
   __shared__ uint32_t s_med[2];
   __shared__ u64 s_total[2];
-  const uint32_t lane = threadIdx.x % 64u, wave = threadIdx.x / 64u;
+  const uint32_t lane = threadIdx.x % 64u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);
   for (uint64_t item = blockIdx.x; item < items; item += gridDim.x) {
     const uint32_t *r0 = hist + 2u * item * kBuckets, *r1 = r0 + kBuckets;
 #pragma unroll 1
-    for (uint32_t b = wave; b < kMedBatches; b += kMedWaves) {
+    for (uint32_t b = wave; b < kMedBatches; b += blockDim.x / 64u) {
       u64 s0, s1;
       batch_sums(r0, r1, b, lane, s0, s1);
       s0 = wave_sum(s0);
@@ -1294,6 +1315,7 @@ __global__ __launch_bounds__(64 * kMedWaves) void median_kernel(const uint32_t *
         if (median) median[2u * item + d] = s_med[d];
         if (s_total[d] >= need && (u64)s_med[d] * kBucketBps < threshold) f |= (uint8_t)(1u << d);
       }
+      if (prev) f |= (uint8_t)((f & prev[item] & 3u) << 2);
       flags[item] = f;
     }
   }
@@ -1796,10 +1818,24 @@ extern "C" int gnm_median_flags(const gnm_registry *reg, const uint32_t *rate_hi
   const uint64_t cap = (uint64_t)device_cus(dev) * 16u;
   const uint64_t blocks = items;
   const uint64_t need = min_bulk_flows > 1 ? min_bulk_flows : 1;
-  hipLaunchKernelGGL(median_kernel, dim3((uint32_t)(blocks < cap ? blocks : cap)), dim3(64 * kMedWaves), 0, stream,
-                     rate_hist, items, threshold_bps, need, median_bucket, flags);
+  // With an item or less per CU, a wave per batch: 64 items take 8.8 us (four
+  // waves 9.8), 256 13.3 (13.8); beyond, a larger workgroup only waits longer
+  // at its barriers (1,000 items: 23.7, four waves 20.2).
+  const uint32_t waves = items <= (uint64_t)device_cus(dev) ? kMedBatches : kMedWaves;
+  // One window: the two-window rule needs no other flag byte of this call, so
+  // the median kernel applies it and a launch of 1.9 to 4.7 us goes (unless
+  // `prev_flags` is in an array that this kernel writes).
+  const auto apart = [&](const void *p, uint64_t bytes) {
+    const uintptr_t a = (uintptr_t)p, b = (uintptr_t)prev_flags;
+    return !p || a + bytes <= b || b + items <= a;
+  };
+  const bool warn = n_windows == 1 &&
+                    (!prev_flags || (apart(flags, items) && apart(median_bucket, items * 2u * sizeof(uint32_t))));
+  hipLaunchKernelGGL(median_kernel, dim3((uint32_t)(blocks < cap ? blocks : cap)), dim3(64u * waves), 0, stream,
+                     rate_hist, items, threshold_bps, need, median_bucket, flags, warn ? prev_flags : nullptr);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "median launch");
+  if (warn) return GNM_OK;
   hipLaunchKernelGGL(warn_kernel, dim3((reg->n_sites + 255u) / 256u), dim3(256), 0, stream, flags, n_windows,
                      reg->n_sites, prev_flags);
   e = hipGetLastError();
