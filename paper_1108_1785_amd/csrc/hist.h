@@ -41,7 +41,11 @@ uint64_t hist_work_bytes(uint64_t n, uint64_t grid, uint32_t n_windows, uint32_t
 // Staging arrays inside a work area laid out for (n, grid, n_windows, hist_rows).
 HistStage hist_stage(void *work, uint64_t n, uint64_t grid, uint32_t n_windows, uint32_t hist_rows);
 
-// Kernel attributes of the reduce kernel on device dev (once per device,
+// Whether such a call counts its histograms straight from the staged keys, in
+// one kernel without partitions (and so without partition counts).
+bool hist_direct(uint64_t n, uint64_t grid, uint32_t n_windows, uint32_t hist_rows);
+
+// Kernel attributes of the histogram kernels on device dev (once per device,
 // outside any graph capture).
 hipError_t hist_prepare(int dev);
 

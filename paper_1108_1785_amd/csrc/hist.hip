@@ -22,6 +22,8 @@
 //      rows whole (16-byte stores, zeros included), or adds its counts into
 //      them when the call accumulates; the slices of a split partition add
 //      their non-zero counts with device atomics.
+// A small call leaves the partitions out: hist_direct_kernel counts each row
+// from all the keys.
 // The histograms need no zeroing pass of their own: every row of a call is
 // written by the reduce, or zeroed by the scatter.  (Zeroing them in the
 // classify kernel instead, a few 16-byte stores per tile, measured 15 us
@@ -46,6 +48,15 @@ constexpr uint32_t kRowsMax = 65536;      // rows over all windows of a staged c
 constexpr uint32_t kPartsTarget = 4096;   // partitions above which 2 (then 4) rows share one
 constexpr uint32_t kOwnerPartBits = 14;   // overflow slice owner: slice << 14 | partition (< 16,384)
 constexpr uint32_t kBucketMask = (1u << kHistBucketBits) - 1u;
+
+// Small calls count straight from the staged keys (hist_direct_kernel), at most:
+constexpr uint32_t kDirectThreads = 1024;
+constexpr uint32_t kDirectGrid = 2048;            // classify workgroups (their ranges are held in LDS)
+constexpr uint64_t kDirectRecords = 100u << 10;   // records
+constexpr uint64_t kDirectWork = 1ull << 25;      // records x rows
+constexpr uint32_t kDirectWideRows = 256;         // up to a row per CU: pieces of 2048 keys, else 1024
+constexpr int kDirectDense = 32;                  // lanes with keys of the row that are looked at for equal ones
+constexpr uint32_t kDirectRowWords = (3u + kBuckets + 3u) / 4u * 4u;
 
 static_assert(kBuckets <= kBucketMask + 1u, "a bucket fits the key's low bits");
 
@@ -136,6 +147,40 @@ struct HistPart {
   }
 };
 
+// LDS words [pad, pad + words) to the same words of `out` (16-byte aligned):
+// stored whole, 16 bytes at a time and single words at the ends, or, when
+// accumulating, the non-zero ones added.
+template <uint32_t THREADS>
+__device__ __forceinline__ void write_rows(const uint32_t *h, uint32_t *out, uint32_t pad, uint32_t words,
+                                           uint32_t accumulate) {
+  if (accumulate) {
+    for (uint32_t i = pad + threadIdx.x; i < pad + words; i += THREADS) {
+      const uint32_t c = h[i];
+      if (c) out[i] += c;
+    }
+    return;
+  }
+  const uint32_t quads = (pad + words + 3u) / 4u;
+  for (uint32_t i = threadIdx.x; i < quads; i += THREADS) {
+    const u32x4 c = ((const u32x4 *)h)[i];
+    if (4u * i >= pad && 4u * i + 4u <= pad + words) {
+      ((u32x4 *)out)[i] = c;
+    } else {
+      const uint32_t cw[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+      for (uint32_t j = 0; j < 4u; ++j)
+        if (4u * i + j >= pad && 4u * i + j < pad + words) out[4u * i + j] = cw[j];
+    }
+  }
+}
+
+struct Direct {
+  const uint32_t *key, *count;  // staged keys; keys of each classify workgroup
+  uint64_t n;
+  uint32_t grid, pieces, accumulate;  // pieces of KEYS keys that the longest range can have
+  uint32_t *hist;
+};
+
 struct Reduce {
   const uint32_t *part, *ptotal, *pbase, *owner;
   const u64 *over;
@@ -210,26 +255,116 @@ __global__ __launch_bounds__(THREADS) void hist_reduce_kernel(const Reduce q) {
       const uint32_t c = h[i];
       if (c) __hip_atomic_fetch_add(out + i, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-  } else if (q.accumulate) {
-    for (uint32_t i = pad + threadIdx.x; i < pad + words; i += THREADS) {
-      const uint32_t c = h[i];
-      if (c) out[i] += c;
-    }
   } else {
-    // the rows whole: 16-byte stores, single words at the ends
-    for (uint32_t i = threadIdx.x; i < quads; i += THREADS) {
-      const u32x4 c = ((const u32x4 *)h)[i];
-      if (4u * i >= pad && 4u * i + 4u <= pad + words) {
-        ((u32x4 *)out)[i] = c;
-      } else {
-        const uint32_t cw[4] = {c.x, c.y, c.z, c.w};
-#pragma unroll
-        for (uint32_t j = 0; j < 4u; ++j)
-          if (4u * i + j >= pad && 4u * i + j < pad + words) out[4u * i + j] = cw[j];
-      }
-    }
+    write_rows<THREADS>(h, out, pad, words, q.accumulate);
   }
 }
+
+// A small call's histograms straight from the staged keys: workgroup = one
+// row, which reads every key of the call, counts its own in an LDS copy of the
+// row and writes the row whole (or adds, when the call accumulates).  The
+// waves take the classify workgroups' ranges in pieces of KEYS keys, the next
+// piece's loads in flight while one is counted.
+// Bound by every CU reading all the keys, written by other XCDs, a piece per
+// memory latency (one piece in flight per wave, or pieces of 1024 where 109
+// registers leave the CU its one workgroup anyway: 2 to 3 us more at 100 k
+// records).  For the classify call and the medians on 64 sites (128 rows), with
+// the partition kernels and so: 1 k records 27.7 and 21.6 us, 10 k 31.0 and
+// 25.2, 100 k 33.5 and 29.5.
+template <uint32_t KEYS>
+__global__ __launch_bounds__(kDirectThreads) void hist_direct_kernel(const Direct q) {
+  extern __shared__ __align__(16) uint32_t h[];  // the row, then the ranges' counts and first keys
+  const uint32_t lane = threadIdx.x % 64u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);
+  const uint32_t row = blockIdx.x;
+  const uint64_t w0 = (uint64_t)row * kBuckets;
+  const uint32_t pad = (uint32_t)(w0 & 3u), quads = (pad + kBuckets + 3u) / 4u;
+  uint32_t *s_count = h + kDirectRowWords, *s_first = s_count + q.grid;
+  for (uint32_t b = threadIdx.x; b < q.grid; b += kDirectThreads) {
+    s_count[b] = q.count[b];
+    s_first[b] = (uint32_t)slice_lo(b, q.n, q.grid);
+  }
+  for (uint32_t i = threadIdx.x; i < quads; i += kDirectThreads) ((u32x4 *)h)[i] = u32x4{0u, 0u, 0u, 0u};
+  __syncthreads();
+  const uint32_t row_key = row << kHistBucketBits, none = row_key + kBuckets;  // no key of this row
+  // Where many lanes have keys of the row, the lanes with the first such
+  // lane's bucket count as one addition, and again of those left, so that a
+  // row of one or two hot buckets doesn't wait for a cell once per key.
+  auto add = [&](uint32_t key) {
+    uint32_t c = key - row_key;
+    u64 in = __ballot(c < kBuckets);
+    if (__popcll(in) >= kDirectDense) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        if (in == 0ull) break;
+        const uint32_t first = (uint32_t)__ffsll((unsigned long long)in) - 1u;
+        const uint32_t c0 = (uint32_t)__builtin_amdgcn_readlane((int)c, first);
+        const u64 same = __ballot(c == c0);
+        if (lane == first) atomicAdd(&h[pad + c0], (uint32_t)__popcll(same));
+        if (c == c0) c = kBuckets;
+        in &= ~same;
+      }
+    }
+    if (c < kBuckets) atomicAdd(&h[pad + c], 1u);
+  };
+  // The wave's next piece that holds keys, from u on: its first quad and its
+  // keys (0 past the last piece: quad 0, which is there to be read).
+  const uint32_t units = q.grid * q.pieces;
+  const u32x4 *key4 = (const u32x4 *)q.key;
+  auto next = [&](uint32_t &u, uint32_t &quad, uint32_t &left) {
+    quad = left = 0u;
+    for (; u < units && left == 0u; u += kDirectThreads / 64u) {
+      const uint32_t b = u / q.pieces, first = (u - b * q.pieces) * KEYS, cnt = s_count[b];
+      if (first < cnt) {
+        left = __builtin_amdgcn_readfirstlane(cnt - first < KEYS ? cnt - first : KEYS);
+        quad = __builtin_amdgcn_readfirstlane((s_first[b] + first) / 4u);  // ranges start at multiples of 4
+      }
+    }
+  };
+  constexpr uint32_t Q = KEYS / 256u;
+  auto load = [&](u32x4 (&v)[Q], uint32_t quad, uint32_t left) {  // past the last key: its quad again
+    const uint32_t last = left ? (left - 1u) / 4u : 0u;
+#pragma unroll
+    for (uint32_t j = 0; j < Q; ++j) {
+      const uint32_t i = j * 64u + lane;
+      v[j] = key4[(uint64_t)quad + (i < last ? i : last)];
+    }
+  };
+  auto count = [&](const u32x4 (&v)[Q], uint32_t left) {
+#pragma unroll
+    for (uint32_t j = 0; j < Q; ++j) {
+      if (j * 256u >= left) break;
+      const uint32_t i = j * 256u + 4u * lane;
+      if ((j + 1u) * 256u <= left) {
+        add(v[j].x);
+        add(v[j].y);
+        add(v[j].z);
+        add(v[j].w);
+      } else {
+        add(i < left ? v[j].x : none);
+        add(i + 1u < left ? v[j].y : none);
+        add(i + 2u < left ? v[j].z : none);
+        add(i + 3u < left ? v[j].w : none);
+      }
+    }
+  };
+  u32x4 va[Q], vb[Q];
+  uint32_t u = wave, quad, la, lb;
+  next(u, quad, la);
+  load(va, quad, la);
+  while (la) {
+    next(u, quad, lb);
+    load(vb, quad, lb);
+    count(va, la);
+    if (lb == 0u) break;
+    next(u, quad, la);
+    load(va, quad, la);
+    count(vb, lb);
+  }
+  __syncthreads();
+  write_rows<kDirectThreads>(h, q.hist + (w0 - pad), pad, kBuckets, q.accumulate);
+}
+
+uint32_t direct_lds_bytes(uint64_t grid) { return 4u * (kDirectRowWords + 2u * (uint32_t)grid); }
 
 uint32_t reduce_lds_bytes(uint32_t shift) { return ((3u + (kBuckets << shift) + 3u) / 4u) * 16u; }
 
@@ -242,6 +377,19 @@ bool hist_stage_fits(uint64_t n, uint32_t n_windows, uint32_t hist_rows) {
 
 uint64_t hist_work_bytes(uint64_t n, uint64_t grid, uint32_t n_windows, uint32_t hist_rows) {
   return layout(n, grid, plan(n, n_windows, hist_rows)).end;
+}
+
+// Three launches cost more than reading every key once per row, up to the
+// lines below (classify call and medians, with the partition kernels and with
+// hist_direct_kernel).  Records x rows: 16,384 on 2,000 rows 55.6 and 51.4 us,
+// 65,536 on 512 rows 42.0 and 37.8, but 30,000 on 2,000 rows 55.8 and 53.9 and
+// 100,000 57.5 and 70.9.  Records: what one row's workgroup may have to count;
+// 100,000 flows that are all bulk (classify call alone) take as long either
+// way, spread over 64 sites (26.0 and 26.0) or in one row (68.2 and 67.0),
+// 131,072 more (26.3 and 28.6, 65.3 and 77.0).
+bool hist_direct(uint64_t n, uint64_t grid, uint32_t n_windows, uint32_t hist_rows) {
+  const uint64_t rows = (uint64_t)n_windows * hist_rows;
+  return grid <= kDirectGrid && n <= kDirectRecords && n * rows <= kDirectWork;
 }
 
 HistStage hist_stage(void *work, uint64_t n, uint64_t grid, uint32_t n_windows, uint32_t hist_rows) {
@@ -262,6 +410,9 @@ hipError_t hist_prepare(int dev) {
   if (e == hipSuccess)
     e = hipFuncSetAttribute((const void *)hist_reduce_kernel<1024>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)reduce_lds_bytes(2));
+  for (const void *f : {(const void *)hist_direct_kernel<1024>, (const void *)hist_direct_kernel<2048>})
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)direct_lds_bytes(kDirectGrid));
   if (e == hipSuccess && dev >= 0 && dev < 64) done[dev] = true;
   return e;
 }
@@ -271,6 +422,25 @@ int hist_pipeline_launch(void *work, uint64_t n, uint64_t grid, uint32_t n_windo
   const Plan pl = plan(n, n_windows, hist_rows);
   const Layout L = layout(n, grid, pl);
   char *w = (char *)work;
+  if (hist_direct(n, grid, n_windows, hist_rows)) {
+    Direct d{};
+    d.key = (const uint32_t *)(w + L.part.stage);
+    d.count = (const uint32_t *)(w + L.part.scount);
+    d.n = n;
+    d.grid = (uint32_t)grid;
+    const uint32_t keys = pl.total_rows <= kDirectWideRows ? 2048u : 1024u;
+    d.pieces = (uint32_t)(((n + grid - 1u) / grid + 3u + keys - 1u) / keys);
+    d.accumulate = accumulate ? 1u : 0u;
+    d.hist = hist;
+    hipLaunchKernelGGL(keys == 2048u ? hist_direct_kernel<2048> : hist_direct_kernel<1024>, dim3(pl.total_rows),
+                       dim3(kDirectThreads), direct_lds_bytes(grid), stream, d);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+      set_last_error(std::string("histogram kernel: ") + hipGetErrorString(e));
+      return GNM_E_HIP;
+    }
+    return GNM_OK;
+  }
   PartArgs<uint32_t> pa{};
   pa.stage = (const uint32_t *)(w + L.part.stage);
   pa.scount = (const uint32_t *)(w + L.part.scount);
