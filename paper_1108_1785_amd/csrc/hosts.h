@@ -1,7 +1,7 @@
 // Per-host statistics and medians: the interface between the classify
 // launcher (kernels.hip) and the per-host kernels (hosts.hip).
 //
-// The classify kernel appends one entry (host key, bytes, rate, bucket) per bulk flow
+// The classify kernel appends one entry (host, bytes, duration) per bulk flow
 // of a registered site to its workgroup's staging range: workgroup b owns
 // entries [lo_b, lo_b + count[b]) of the staging arrays, where [lo_b, hi_b)
 // is its slice of the records (a record gives at most one entry, so the range
@@ -17,13 +17,27 @@
 
 namespace gnm {
 
-// One staged bulk flow: 32 bytes, written and read as two 16-byte words.
-struct __attribute__((aligned(32))) HostEntry {
-  unsigned long long key;    // remote address << 32 | row (2 * site + direction)
-  unsigned long long bytes;
-  unsigned long long rate;   // bits/s
-  unsigned long long bucket; // the rate's 10 kbps bucket
+// One staged bulk flow: one 16-byte word.  The rate and its bucket follow from
+// bytes and duration.  `y` holds, from the top, a bit that is set when the
+// bytes do not fit, the row (2 * site + direction) from bit `vbits` on, and
+// below it the bytes, or the record's index when they do not fit.  `vbits` is
+// the launch's: 63 less the bits of a row.  (With 32-byte entries that carried
+// rate and bucket too, a 10 M-record window of 1.4 M such flows took 3 us more
+// in the classify kernel, which stores them, and 36 us instead of 29 in the
+// scatter.)
+struct __attribute__((aligned(16))) HostEntry {
+  unsigned long long x;  // remote address << 32 | duration in ms
+  unsigned long long y;
 };
+constexpr unsigned long long kHostWide = 1ull << 63;
+
+// Bits of a HostEntry's bytes for `rows` rows.  (Rows take at most 30 bits, so
+// that a record's index always fits: 2^33 records would be 240 GB.)
+inline uint32_t host_value_bits(uint32_t rows) {
+  uint32_t b = 1;
+  while (b < 30u && (rows - 1u) >> b) ++b;
+  return 63u - b;
+}
 
 // Staging arrays written by the classify kernel (device pointers into the
 // caller's work buffer).
@@ -48,7 +62,9 @@ HostStage host_stage(void *work, uint64_t n, uint64_t grid);
 // (left out when the classify kernel counted its entries per partition and
 // cleared ht->counters itself: `counted`), their scan, the scatter into
 // partition order and the per-partition reduction into ht's arrays.  With
-// n == 0 only the counters are cleared.
-int host_pipeline_launch(const gnm_host_table *ht, uint64_t n, uint64_t grid, bool counted, hipStream_t stream);
+// n == 0 only the counters are cleared.  bytes: the records' byte counts;
+// rows: the table's rows of registered sites.
+int host_pipeline_launch(const gnm_host_table *ht, uint64_t n, uint64_t grid, const uint64_t *bytes, uint32_t rows,
+                         bool counted, hipStream_t stream);
 
 }  // namespace gnm

@@ -5,8 +5,8 @@
 // Dense bucket arrays per host do not fit (a 10 M-record window has about
 // half a million hosts with bulk flows; 10,001 buckets each would be 21 GB),
 // and hash-table updates with device-scope atomics are bound by the rate of
-// those atomics.  Here the classify kernel only appends one 32-byte entry
-// (host key, bytes, rate, bucket) per bulk flow of a registered site to its
+// those atomics.  Here the classify kernel only appends one 16-byte entry
+// (host, bytes, duration) per bulk flow of a registered site to its
 // workgroup's staging range, and four kernels finish the job with no
 // per-flow device atomics:
 //   1. part_count_kernel: per classify workgroup, the number of its entries
@@ -41,6 +41,7 @@
 #include "gnm_device.h"
 #include "hosts.h"
 #include "partition.h"
+#include "rate.h"
 #include "registry.h"
 
 namespace gnm {
@@ -64,13 +65,18 @@ constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 
 typedef u64 u64x2 __attribute__((ext_vector_type(2)));
 
+// Key of an entry's host: remote address << 32 | row.
+__device__ __forceinline__ u64 entry_key(u64 x, u64 y, uint32_t vbits) {
+  return (x & ~0xFFFFFFFFull) | ((y & ~(u64)kHostWide) >> vbits);
+}
+
 // Partition of a host entry: the top pbits of a hash of its key, so all
 // entries of a host land in one partition.
 struct HostPart {
-  uint32_t pbits;
+  uint32_t pbits, vbits;
   static constexpr bool kTotalsHook = false;
   static __device__ __forceinline__ uint32_t part(const HostEntry &e, const HostPart &t) {
-    return (uint32_t)(mix64(e.key) >> (64u - t.pbits));
+    return (uint32_t)(mix64(entry_key(e.x, e.y, t.vbits)) >> (64u - t.pbits));
   }
 };
 
@@ -81,19 +87,15 @@ struct Parts {
   uint32_t *median;
   uint64_t capacity;
   u64 *counters;
+  const uint64_t *bytes;  // of the records
+  uint32_t vbits;
 };
 
-__device__ __forceinline__ void load_entry(const HostEntry *e, u64 &key, u64 &bytes, u64 &rate, uint32_t &bucket) {
-  const u64x2 a = *(const u64x2 *)e, b = *((const u64x2 *)e + 1);
-  key = a.x;
-  bytes = a.y;
-  rate = b.x;
-  bucket = (uint32_t)b.y;
-}
-
-__device__ __forceinline__ void store_entry(HostEntry *e, u64 key, u64 bytes, u64 rate, uint32_t bucket) {
-  *(u64x2 *)e = u64x2{key, bytes};
-  *((u64x2 *)e + 1) = u64x2{rate, (u64)bucket};
+// Bytes and rate of an entry.
+__device__ __forceinline__ void entry_rate(const Parts &q, u64x2 e, u64 &bytes, u64 &rate) {
+  bytes = e.y & ((1ull << q.vbits) - 1ull);
+  if (e.y & kHostWide) bytes = q.bytes[bytes];
+  rate = rate_bps(bytes, (uint32_t)e.x);
 }
 
 struct HostMap {
@@ -192,18 +194,17 @@ struct Shared {
 // before the block's end, so no entry is overwritten unread.
 template <uint32_t SLOTS>
 __device__ __forceinline__ void compact_deferred(HostEntry *ent, uint32_t n, uint32_t nmax, const u64 *keys,
-                                                 uint32_t *deferred, uint32_t tid) {
+                                                 uint32_t vbits, uint32_t *deferred, uint32_t tid) {
   for (uint32_t i0 = 0; i0 < nmax; i0 += kHostThreads) {
     const uint32_t i = i0 + tid;
-    u64 key = 0, by = 0, rt = 0;
-    uint32_t bk = 0;
+    u64x2 e{0ull, 0ull};
     bool keep = false;
     if (i < n) {
-      load_entry(ent + i, key, by, rt, bk);
-      keep = map_find<SLOTS>(keys, key) == kNoSlot;
+      e = *(const u64x2 *)(ent + i);
+      keep = map_find<SLOTS>(keys, entry_key(e.x, e.y, vbits)) == kNoSlot;
     }
     __syncthreads();
-    if (keep) store_entry(ent + atomicAdd(deferred, 1u), key, by, rt, bk);
+    if (keep) *(u64x2 *)(ent + atomicAdd(deferred, 1u)) = e;
     __syncthreads();
   }
 }
@@ -263,29 +264,30 @@ __device__ __forceinline__ void reduce_lists(ListMap &m, Shared &sh, const Parts
 #pragma unroll
   for (uint32_t r = 0; r < kRounds; ++r) {
     if (r * kPerThread * kHostThreads >= n) break;
-    u64 key[kPerThread], by[kPerThread], rt[kPerThread];
-    uint32_t bk[kPerThread];
+    u64x2 v[kPerThread];
 #pragma unroll
     for (uint32_t j = 0; j < kPerThread; ++j) {
       const uint32_t i = (r * kPerThread + j) * kHostThreads + tid;
-      if (i < n) load_entry(ent + i, key[j], by[j], rt[j], bk[j]);
+      if (i < n) v[j] = *(const u64x2 *)(ent + i);
     }
 #pragma unroll
     for (uint32_t j = 0; j < kPerThread; ++j) {
       const uint32_t e = r * kPerThread + j, i = e * kHostThreads + tid;
       sb[e] = kNoSlot;
       if (i >= n) continue;
-      const uint32_t s = map_insert<kListSlots>(m.key, key[j]);
+      const uint32_t s = map_insert<kListSlots>(m.key, entry_key(v[j].x, v[j].y, q.vbits));
       if (s == kNoSlot) {
         sh.overflow[g] = 1u;
         continue;
       }
-      sb[e] = (s << 14) | bk[j];
       place[e] = atomicAdd(&m.flows[s], 1u);
-      atomicAdd(&m.stat[0][s], by[j]);
-      atomicAdd(&m.stat[1][s], rt[j]);
-      atomicMin(&m.stat[2][s], rt[j]);
-      atomicMax(&m.stat[3][s], rt[j]);
+      u64 bytes, rate;
+      entry_rate(q, v[j], bytes, rate);
+      sb[e] = (s << 14) | rate_bucket(rate);
+      atomicAdd(&m.stat[0][s], bytes);
+      atomicAdd(&m.stat[1][s], rate);
+      atomicMin(&m.stat[2][s], rate);
+      atomicMax(&m.stat[3][s], rate);
     }
   }
   __syncthreads();
@@ -377,7 +379,8 @@ __device__ __forceinline__ void reduce_lists(ListMap &m, Shared &sh, const Parts
     const uint32_t h = i / 5u, f = i - 5u * h, s = m.slot[h];
     q.stats[5u * out + i] = f == 0u ? (u64)m.flows[s] : m.stat[f - 1u][s];
   }
-  compact_deferred<kListSlots>(ent, sh.overflow[g] ? n : 0u, any_overflow(sh) ? nmax : 0u, m.key, &sh.deferred[g], tid);
+  compact_deferred<kListSlots>(ent, sh.overflow[g] ? n : 0u, any_overflow(sh) ? nmax : 0u, m.key, q.vbits,
+                               &sh.deferred[g], tid);
 }
 
 // One batch of a larger partition (a hot host): every digit round re-reads
@@ -401,28 +404,29 @@ __device__ __forceinline__ void reduce_radix(HostMap &m, Shared &sh, const Parts
   // hosts, statistics and the first digit (bits 13..12) of every bucket;
   // each thread loads kPerThread entries before it works on them
   for (uint32_t i0 = 0; i0 < n; i0 += kPerThread * kHostThreads) {
-    u64 key[kPerThread], by[kPerThread], rt[kPerThread];
-    uint32_t bk[kPerThread];
+    u64x2 v[kPerThread];
 #pragma unroll
     for (uint32_t j = 0; j < kPerThread; ++j) {
       const uint32_t i = i0 + j * kHostThreads + tid;
-      if (i < n) load_entry(ent + i, key[j], by[j], rt[j], bk[j]);
+      if (i < n) v[j] = *(const u64x2 *)(ent + i);
     }
 #pragma unroll
     for (uint32_t j = 0; j < kPerThread; ++j) {
       const uint32_t i = i0 + j * kHostThreads + tid;
       if (i >= n) continue;
-      const uint32_t s = map_insert<kHostSlots>(m.key, key[j]);
+      const uint32_t s = map_insert<kHostSlots>(m.key, entry_key(v[j].x, v[j].y, q.vbits));
       if (s == kNoSlot) {
         sh.overflow[g] = 1u;
         continue;
       }
+      u64 bytes, rate;
+      entry_rate(q, v[j], bytes, rate);
       atomicAdd(&m.flows[s], 1u);
-      atomicAdd(&m.bytes[s], (u64)by[j]);
-      atomicAdd(&m.rsum[s], (u64)rt[j]);
-      atomicMin(&m.rmin[s], (u64)rt[j]);
-      atomicMax(&m.rmax[s], (u64)rt[j]);
-      atomicAdd(&m.bins[bk[j] >> 12][s], 1u);
+      atomicAdd(&m.bytes[s], bytes);
+      atomicAdd(&m.rsum[s], rate);
+      atomicMin(&m.rmin[s], rate);
+      atomicMax(&m.rmax[s], rate);
+      atomicAdd(&m.bins[rate_bucket(rate) >> 12][s], 1u);
     }
   }
   __syncthreads();
@@ -446,11 +450,12 @@ __device__ __forceinline__ void reduce_radix(HostMap &m, Shared &sh, const Parts
   for (uint32_t r = 1; r < kDigitRounds; ++r) {
     const uint32_t shift = 12u - 4u * r;
     for (uint32_t i = tid; i < n; i += kHostThreads) {
-      uint32_t bk;
-      u64 key, by, rate;
-      load_entry(ent + i, key, by, rate, bk);
-      const uint32_t s = map_find<kHostSlots>(m.key, key);
+      const u64x2 e = *(const u64x2 *)(ent + i);
+      const uint32_t s = map_find<kHostSlots>(m.key, entry_key(e.x, e.y, q.vbits));
       if (s == kNoSlot) continue;
+      u64 bytes, rate;
+      entry_rate(q, e, bytes, rate);
+      const uint32_t bk = rate_bucket(rate);
       if ((bk >> (shift + 4u)) == m.prefix[s]) atomicAdd(&m.bins[(bk >> shift) & 15u][s], 1u);
     }
     __syncthreads();
@@ -473,15 +478,16 @@ __device__ __forceinline__ void reduce_radix(HostMap &m, Shared &sh, const Parts
       if (q.median) q.median[idx] = m.prefix[tid];
     }
   }
-  compact_deferred<kHostSlots>(ent, sh.overflow[g] ? n : 0u, any_overflow(sh) ? nmax : 0u, m.key, &sh.deferred[g], tid);
+  compact_deferred<kHostSlots>(ent, sh.overflow[g] ? n : 0u, any_overflow(sh) ? nmax : 0u, m.key, q.vbits,
+                               &sh.deferred[g], tid);
 }
 
 // One workgroup per kHostGroups partitions, a group of kHostThreads lanes for
 // each.  Small partitions take batches of lists together; large ones then
 // batches of the radix selection.
 // A window of 10 M records (4,096 partitions of 344 entries, 127 hosts) is
-// bound by the latency of a workgroup's steps and by the one counter:
-// 61.7 us with a radix selection for every partition; with lists 67 us at one
+// bound by the latency of a workgroup's steps and by the one counter (entries
+// of half the size, as now, changed nothing): 61.7 us with a radix selection for every partition; with lists 67 us at one
 // partition per workgroup (42 without the counter's atomics), 51.7 at two,
 // 56 at four (whose barriers wait for the slowest of four).  One of 1 M
 // records of the 64-site registry (512 partitions of 275 entries, nearly as
@@ -546,7 +552,8 @@ HostStage host_stage(void *work, uint64_t n, uint64_t grid) {
                    host_part_bits(n)};
 }
 
-int host_pipeline_launch(const gnm_host_table *ht, uint64_t n, uint64_t grid, bool counted, hipStream_t stream) {
+int host_pipeline_launch(const gnm_host_table *ht, uint64_t n, uint64_t grid, const uint64_t *bytes, uint32_t rows,
+                         bool counted, hipStream_t stream) {
   if (n == 0) {
     hipLaunchKernelGGL(host_clear_kernel, dim3(1), dim3(1), 0, stream, (u64 *)ht->counters);
   } else {
@@ -557,7 +564,7 @@ int host_pipeline_launch(const gnm_host_table *ht, uint64_t n, uint64_t grid, bo
     pa.scount = (const uint32_t *)(w + L.scount);
     pa.n = n;
     pa.grid = (uint32_t)grid;
-    const HostPart hp{host_part_bits(n)};
+    const HostPart hp{host_part_bits(n), host_value_bits(rows)};
     pa.nparts = 1u << hp.pbits;
     pa.phist = (uint32_t *)(w + L.phist);
     pa.ptotal = (uint32_t *)(w + L.ptotal);
@@ -575,6 +582,8 @@ int host_pipeline_launch(const gnm_host_table *ht, uint64_t n, uint64_t grid, bo
     q.median = ht->median;
     q.capacity = ht->capacity;
     q.counters = (u64 *)ht->counters;
+    q.bytes = bytes;
+    q.vbits = hp.vbits;
     const uint32_t P = pa.nparts;
     if (!counted)
       hipLaunchKernelGGL((part_count_kernel<HostEntry, HostPart>), dim3((uint32_t)grid), dim3(kPartThreads), P * 4u,

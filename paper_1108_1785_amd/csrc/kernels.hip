@@ -106,6 +106,7 @@ struct ClassifyArgs {
   uint32_t *hist;      // rate histograms: n_windows * hist_rows * kBuckets counts (FEAT & kFeatHist)
   uint32_t hist_rows;  // 2 * n_sites: rows of registered sites
   uint32_t lds_off_hist, hist_slots;  // LDS histogram cache (0 slots: every count goes to device memory)
+  uint32_t hs_vbits;                  // HostEntry: bits of the bytes
   HostEntry *hs_entry;                // per-host staging (FEAT & kFeatHosts): workgroup b's entries
   uint32_t *hs_count;                 //   at [lo_b, lo_b + hs_count[b]) of its record slice [lo_b, hi_b)
   char *ts_entry;                     // spilled rows (a table beyond LDS, with a workspace; NULL: device
@@ -725,19 +726,11 @@ __device__ __forceinline__ uint32_t reserve_hosts(uint32_t *cursor, const bool (
   return __builtin_amdgcn_readfirstlane(base);
 }
 
-// One staged entry: two 16-byte stores.
-__device__ __forceinline__ void stage_host(const Lds &L, uint32_t pos, uint64_t key, uint64_t bytes, uint64_t rate) {
-  typedef u64 u64x2_ __attribute__((ext_vector_type(2)));
-  u64x2_ *e = (u64x2_ *)(L.se + pos);
-  e[0] = u64x2_{(u64)key, (u64)bytes};
-  e[1] = u64x2_{(u64)rate, (u64)rate_bucket(rate)};
-}
-
-// Aggregate the tile's classified records.
-template <int R, bool ACC_LDS, uint32_t FEAT>
+// Aggregate the tile's classified records; at(k): index of the lane's k-th.
+template <int R, bool ACC_LDS, uint32_t FEAT, class At>
 __device__ __forceinline__ void aggregate_tile(const Addr<R> &t, const uint32_t (&row)[R], const Rest<R> &r,
                                                const ClassifyArgs &a, const Lds &L, u64 *g_tab,
-                                               uint32_t *h_tab) {
+                                               uint32_t *h_tab, const At &at) {
   const bool(&valid)[R] = t.v;
   uint32_t durv[R];
   bool bulkv[R];
@@ -802,21 +795,25 @@ __device__ __forceinline__ void aggregate_tile(const Addr<R> &t, const uint32_t 
           hist_add(L, h_tab, row[k], rate_bucket(rate));
       }
       if (HOSTS && row[k] < a.hist_rows) {
-        const uint64_t key = ((uint64_t)((row[k] & 1u) ? t.d[k] : t.s[k]) << 32) | row[k];
-        stage_host(L, hpos + (uint32_t)__builtin_popcountll(hb[k] & below), key, r.b[k], rate);
-        if (L.hp) atomicAdd(&L.hp[(uint32_t)(mix64(key) >> (64u - L.hpbits))], 1u);
+        // one 16-byte store
+        typedef u64 u64x2_ __attribute__((ext_vector_type(2)));
+        const uint64_t host = (uint64_t)((row[k] & 1u) ? t.d[k] : t.s[k]) << 32;
+        const uint64_t v = (r.b[k] >> a.hs_vbits) == 0u ? r.b[k] : kHostWide | at(k);
+        *(u64x2_ *)(L.se + hpos + (uint32_t)__builtin_popcountll(hb[k] & below)) =
+            u64x2_{host | dur, v | ((uint64_t)row[k] << a.hs_vbits)};
+        if (L.hp) atomicAdd(&L.hp[(uint32_t)(mix64(host | row[k]) >> (64u - L.hpbits))], 1u);
       }
     }
     if (HOSTS || kst) hpos += (uint32_t)__builtin_popcountll(hb[k]);
   }
 }
 
-template <int R, int LAY, bool ACC_LDS, uint32_t FEAT>
+template <int R, int LAY, bool ACC_LDS, uint32_t FEAT, class At>
 __device__ __forceinline__ void process_tile(const Addr<R> &t, const Rest<R> &r, const ClassifyArgs &a,
-                                             const Lds &L, u64 *g_tab, uint32_t *h_tab) {
+                                             const Lds &L, u64 *g_tab, uint32_t *h_tab, const At &at) {
   uint32_t row[R];
   classify_tile<R, LAY>(t, a, L, row);
-  aggregate_tile<R, ACC_LDS, FEAT>(t, row, r, a, L, g_tab, h_tab);
+  aggregate_tile<R, ACC_LDS, FEAT>(t, row, r, a, L, g_tab, h_tab, at);
 }
 
 // Records [lo, hi) of one window: tiles whose addresses are prefetched one
@@ -837,7 +834,9 @@ __device__ __forceinline__ void process_range(const ClassifyArgs &a, const Lds &
     load_addr<R, VEC>(nxt, a, base + T, hi);  // past the end: reloads the last records, marked invalid
     uint32_t row[R];
     classify_tile<R, LAY>(cur, a, L, row);
-    aggregate_tile<R, ACC_LDS, FEAT>(cur, row, rest, a, L, g_tab, h_tab);
+    aggregate_tile<R, ACC_LDS, FEAT>(cur, row, rest, a, L, g_tab, h_tab, [&](int k) -> uint64_t {
+      return VEC ? base + 4ull * threadIdx.x + k : base + (uint64_t)k * kThreads + threadIdx.x;
+    });
     cur = nxt;
   }
 }
@@ -974,8 +973,9 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const ClassifyArgs a
         Addr<R> m;
         Rest<R> mr;
         const bool head = tid < a0 - i, tail = tid >= 3 && tid - 3 < seg_end - a1;
-        load_single(m, mr, a, head ? i + tid : a1 + (tid - 3), head || tail);
-        process_tile<R, LAY, ACC_LDS, FEAT>(m, mr, a, L, g_tab, h_tab);
+        const uint64_t idx = head ? i + tid : a1 + (tid - 3);
+        load_single(m, mr, a, idx, head || tail);
+        process_tile<R, LAY, ACC_LDS, FEAT>(m, mr, a, L, g_tab, h_tab, [&](int) -> uint64_t { return idx; });
       }
       if (a0 < a1) process_range<4, true, LAY, ACC_LDS, FEAT>(a, L, g_tab, h_tab, a0, a1);
     } else {
@@ -1568,6 +1568,7 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
   if (ht) {
     const HostStage st = host_stage(ht->work, rec->n, grid);
     a.hs_entry = st.entry;
+    a.hs_vbits = host_value_bits(a.hist_rows);
     a.hs_count = st.count;
   }
   // a table beyond LDS with a workspace that holds its spilled rows: the
@@ -1705,7 +1706,7 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
   // the per-host kernels, after the classify launch (and on an empty run)
   auto count_hosts = [&]() -> int {
     if (!ht) return GNM_OK;
-    return host_pipeline_launch(ht, rec->n, grid, a.hp_hist != nullptr, stream);
+    return host_pipeline_launch(ht, rec->n, grid, rec->bytes, a.hist_rows, a.hp_hist != nullptr, stream);
   };
   // the mean-rate flags, when the reduce kernel does not apply them
   auto flag_launch = [&]() -> int {
