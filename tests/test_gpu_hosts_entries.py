@@ -37,3 +37,16 @@ def test_bytes_limit(torch_cuda, n_sites, n, hosts, rpt, grid):  # noqa: F811
     reg, orc = gnm.Registry(*args), oracle.Registry(*args)
     t, _ = run(reg, rec, 1 << 14, off=off, records_per_thread=rpt, grid_blocks=grid)
     check(t, orc, rec)
+
+
+@pytest.mark.parametrize("grid", [1, 7, 8, 9, 31, 64, 250, 1023])
+def test_workgroup_orders(torch_cuda, grid):  # noqa: F811
+    # shares of a partition ordered by workgroup modulo 8: grids below, at and
+    # beside multiples of 8, and with more workgroups per wave than it keeps
+    say("case: host entries on", grid, "workgroups")
+    rng = np.random.default_rng(grid)
+    args = ([0x0B000000, 0x0C000000], [8, 8], [0, 1], 2, [0x0A000000], [16])
+    remote = (0x0B000000 | rng.integers(0, 4_000, 30_000)).astype(np.uint32)
+    rec = _host_records(remote.size, remote, rng)
+    t, _ = run(gnm.Registry(*args), rec, 1 << 14, grid_blocks=grid)
+    check(t, oracle.Registry(*args), rec)
