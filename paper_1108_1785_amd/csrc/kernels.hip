@@ -61,6 +61,7 @@ constexpr uint32_t kRedRows = 8;     // reduce kernel: table rows (4 sites) per 
 constexpr uint32_t kRedWords = kRedRows * kAccFields;  // reduce kernel: 56 table words, one per lane
 constexpr uint32_t kRedGroups = 16;  // reduce kernel: at most 16 waves, each summing every G-th slot
 constexpr uint32_t kRedUnroll = 8;   // reduce kernel: slot loads in flight per lane
+constexpr uint32_t kSmallTable = 16384;   // bytes of a table that costs a workgroup little to start and merge
 constexpr uint32_t kFeatHist = 1;         // classify_kernel FEAT bits: rate histograms,
 constexpr uint32_t kFeatHosts = 2;        //   per-host statistics
 constexpr uint32_t kHistKeyBits = 14;     // LDS histogram cache key: row << 14 | bucket
@@ -1413,6 +1414,8 @@ hipError_t allow_lds(KernelFn fn, int slot, int dev) {
   return e;
 }
 
+// Workgroups per CU that LDS allows.  The sizes of work areas count on these,
+// as a caller may ask for that many.
 uint32_t blocks_per_cu(const gnm_registry *reg) { return reg->lds_bytes <= kLdsMax / 2 ? 2u : 1u; }
 
 uint64_t partial_bytes(const gnm_registry *reg, uint64_t grid) {
@@ -1424,14 +1427,37 @@ bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 // Workgroups of a classify launch over n records with R records per lane:
 // the caller's count, else one resident wave of workgroups (fewer for short
-// runs).
+// runs).  At R = 4 a lane's registers (about 120) leave a CU one workgroup of
+// 16 waves whatever its LDS, and a second one per CU only starts when the
+// first ends: 10 M records on 64 sites 76.1 us with 512 workgroups, 67.0 with
+// 256; 3 M 38.3 and 30.1, 50 M in 256 windows 303 and 294.
 uint64_t launch_grid(const gnm_registry *reg, uint64_t n, uint32_t R, uint32_t grid_blocks, int dev) {
-  const uint64_t resident = (uint64_t)device_cus(dev) * blocks_per_cu(reg);
+  const uint64_t resident = (uint64_t)device_cus(dev) * (R == 4u ? 1u : blocks_per_cu(reg));
   const uint64_t tiles = (n + (uint64_t)kThreads * R - 1) / ((uint64_t)kThreads * R);
   uint64_t grid = grid_blocks ? grid_blocks : (tiles < resident ? tiles : resident);
   if (grid == 0) grid = 1;
   if (grid > 65535u * 16u) grid = 65535u * 16u;
   return grid;
+}
+
+// Workgroups for an automatic launch of `grid` (a tile each) over n records:
+// two per tile where that leaves CUs idle and the tables are small, so that
+// twice the CUs load half as much each: 300 k records on 64 sites (7 KB a
+// table) 15.9 us with 74 workgroups, 15.5 with 148, 100 k 13.6 and 12.8; on
+// 1,000 sites (112 KB) 300 k take 26.3 with 74 and 27.6 with 128.  Only into
+// work areas that hold that many (a workspace with the tables, and the keys if
+// there are histograms to count; a host table's buffer).
+uint64_t split_tiles(const gnm_registry *reg, uint64_t n, uint64_t grid, uint32_t n_windows, const gnm_params &p,
+                     int dev) {
+  const uint64_t cus = (uint64_t)device_cus(dev), twice = 2u * grid < cus ? 2u * grid : cus;
+  if (n == 0 || grid >= cus || !reg->acc_in_lds || 8ull * kAccFields * reg->rows() > kSmallTable || !p.workspace)
+    return grid;
+  uint64_t need = partial_bytes(reg, twice);
+  const uint32_t hist_rows = 2u * reg->n_sites;
+  if (p.rate_hist && hist_stage_fits(n, n_windows, hist_rows))
+    need = ((need + 255u) & ~255ull) + hist_work_bytes(n, twice, n_windows, hist_rows);
+  const bool holds = p.workspace_bytes >= need && (!p.hosts || p.hosts->work_bytes >= host_work_bytes(n, twice));
+  return holds ? twice : grid;
 }
 
 }  // namespace
@@ -1508,7 +1534,8 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
   if (dev != reg->device) { set_last_error("registry belongs to another device"); return GNM_E_INVAL; }
 
   const uint64_t rows = reg->rows();
-  const uint64_t grid = launch_grid(reg, rec->n, R, p.grid_blocks, dev);
+  uint64_t grid = launch_grid(reg, rec->n, R, p.grid_blocks, dev);
+  if (R == 4u && !p.grid_blocks) grid = split_tiles(reg, rec->n, grid, n_windows, p, dev);
   if ((uint64_t)n_windows * rows * 8u > (uint64_t)INT32_MAX * 256u) {
     set_last_error("accumulator tables too large");
     return GNM_E_INVAL;
