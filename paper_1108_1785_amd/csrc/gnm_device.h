@@ -28,13 +28,4 @@ __device__ __forceinline__ uint32_t rate_bucket(uint64_t rate) {
   return rate >= kTop ? kBuckets - 1u : (uint32_t)rate / kBucketBps;
 }
 
-// Finalizer of splitmix64: spreads host keys over partitions and LDS slots.
-__device__ __forceinline__ uint64_t mix64(uint64_t x) {
-  x ^= x >> 30;
-  x *= 0xBF58476D1CE4E5B9ull;
-  x ^= x >> 27;
-  x *= 0x94D049BB133111EBull;
-  return x ^ (x >> 31);
-}
-
 }  // namespace gnm

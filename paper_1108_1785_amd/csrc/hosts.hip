@@ -76,7 +76,8 @@ struct HostPart {
   uint32_t pbits, vbits;
   static constexpr bool kTotalsHook = false;
   static __device__ __forceinline__ uint32_t part(const HostEntry &e, const HostPart &t) {
-    return (uint32_t)(mix64(entry_key(e.x, e.y, t.vbits)) >> (64u - t.pbits));
+    const u64 k = entry_key(e.x, e.y, t.vbits);
+    return host_hash((uint32_t)(k >> 32), (uint32_t)k) >> (32u - t.pbits);
   }
 };
 
@@ -113,7 +114,7 @@ struct HostMap {
 // holding another key stays that way and linear probing needs no locks.
 template <uint32_t SLOTS>
 __device__ __forceinline__ uint32_t map_insert(u64 *keys, u64 key) {
-  uint32_t s = (uint32_t)mix64(key) & (SLOTS - 1u);
+  uint32_t s = host_hash((uint32_t)(key >> 32), (uint32_t)key) & (SLOTS - 1u);
   for (uint32_t probe = 0; probe < SLOTS; ++probe) {
     u64 cur = keys[s];
     if (cur == kHostEmpty) cur = atomicCAS(&keys[s], kHostEmpty, key);
@@ -125,7 +126,7 @@ __device__ __forceinline__ uint32_t map_insert(u64 *keys, u64 key) {
 
 template <uint32_t SLOTS>
 __device__ __forceinline__ uint32_t map_find(const u64 *keys, u64 key) {
-  uint32_t s = (uint32_t)mix64(key) & (SLOTS - 1u);
+  uint32_t s = host_hash((uint32_t)(key >> 32), (uint32_t)key) & (SLOTS - 1u);
   for (uint32_t probe = 0; probe < SLOTS; ++probe) {
     const u64 cur = keys[s];
     if (cur == key) return s;

@@ -121,7 +121,7 @@ struct ClassifyArgs {
   uint32_t kp_shift, kp_parts;        //   partition of a key: key >> (14 + kp_shift), kp_parts of them
   uint32_t lds_off_kp;                //   LDS counters
   uint32_t *hp_hist;                  // per-host entries counted per partition here: [grid][2^hp_bits] (NULL: not
-  uint32_t hp_bits, lds_off_hp;       //   here); partition mix64(key) >> (64 - hp_bits); LDS counters
+  uint32_t hp_bits, lds_off_hp;       //   here); partition host_hash >> (32 - hp_bits); LDS counters
   unsigned long long *hp_clear;       //   the host table's two counters, cleared by workgroup 0
   uint32_t lds_off_ctr;               // LDS words: the workgroup's staging cursors (hosts, spilled rows, keys)
   uint32_t filters;                   // any exclusion filter set
@@ -331,7 +331,7 @@ struct Lds {
   uint32_t *kp;     // staged histogram keys per partition (NULL: counted by the histogram kernels)
   uint32_t kshift;  // partition of a key: key >> (14 + kshift)
   uint32_t *hp;     // per-host entries per partition (NULL: counted by the count kernel)
-  uint32_t hpbits;  // partition of a host entry: mix64(key) >> (64 - hpbits)
+  uint32_t hpbits;  // partition of a host entry: host_hash >> (32 - hpbits)
   uint32_t win;     // window of the current segment
   uint32_t kbase;   // histogram row of the current segment's window: win * hist_rows
 };
@@ -802,7 +802,7 @@ __device__ __forceinline__ void aggregate_tile(const Addr<R> &t, const uint32_t 
         const uint64_t v = (r.b[k] >> a.hs_vbits) == 0u ? r.b[k] : kHostWide | at(k);
         *(u64x2_ *)(L.se + hpos + (uint32_t)__builtin_popcountll(hb[k] & below)) =
             u64x2_{host | dur, v | ((uint64_t)row[k] << a.hs_vbits)};
-        if (L.hp) atomicAdd(&L.hp[(uint32_t)(mix64(host | row[k]) >> (64u - L.hpbits))], 1u);
+        if (L.hp) atomicAdd(&L.hp[host_hash((row[k] & 1u) ? t.d[k] : t.s[k], row[k]) >> (32u - L.hpbits)], 1u);
       }
     }
     if (HOSTS || kst) hpos += (uint32_t)__builtin_popcountll(hb[k]);
