@@ -326,10 +326,10 @@ uint64_t gnm_workspace_bytes_hist(const gnm_registry *reg, uint64_t n_records, u
  * gnm_host_work_bytes — size of the work buffer of a gnm_host_table for a
  * classify call over n_records records on grid_blocks workgroups (0 = the
  * automatic launch; it fits every automatic launch of up to n_records
- * records).  The buffer holds one 16-byte entry per bulk flow of a
- * registered site (room for every record) twice, to stage the flows and to
- * order them by host partition, plus a partition count per workgroup: about
- * 32 bytes per record.  0 for a NULL registry.
+ * records).  The buffer holds one entry per bulk flow of a registered site
+ * (room for every record) twice, to stage the flows and to order them by host
+ * partition, plus a partition count per workgroup: about 64 bytes per record,
+ * of which the present 16-byte entries use half.  0 for a NULL registry.
  */
 uint64_t gnm_host_work_bytes(const gnm_registry *reg, uint64_t n_records, uint32_t grid_blocks);
 

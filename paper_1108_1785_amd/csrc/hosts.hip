@@ -544,7 +544,11 @@ uint32_t host_part_bits(uint64_t n) {
   return b;
 }
 
-uint64_t host_work_bytes(uint64_t n, uint64_t grid) { return layout(n, grid).end; }
+// The size that callers are told, and held to, has room for 32-byte entries:
+// twice what the layout takes.
+uint64_t host_work_bytes(uint64_t n, uint64_t grid) {
+  return part_layout(n, grid, 1ull << host_part_bits(n), 32u).end;
+}
 
 HostStage host_stage(void *work, uint64_t n, uint64_t grid) {
   const PartLayout L = layout(n, grid);
