@@ -61,9 +61,11 @@ constexpr uint32_t kRedRows = 8;     // reduce kernel: table rows (4 sites) per 
 constexpr uint32_t kRedWords = kRedRows * kAccFields;  // reduce kernel: 56 table words, one per lane
 constexpr uint32_t kRedGroups = 16;  // reduce kernel: at most 16 waves, each summing every G-th slot
 constexpr uint32_t kRedUnroll = 8;   // reduce kernel: slot loads in flight per lane
+constexpr uint64_t kLongRecords = 1ull << 24;  // byte counts of half the memory cache
 constexpr uint32_t kSmallTable = 16384;   // bytes of a table that costs a workgroup little to start and merge
 constexpr uint32_t kFeatHist = 1;         // classify_kernel FEAT bits: rate histograms,
-constexpr uint32_t kFeatHosts = 2;        //   per-host statistics
+constexpr uint32_t kFeatHosts = 2;        //   per-host statistics,
+constexpr uint32_t kFeatLong = 4;         //   neither, and arrays beyond what caches hold
 constexpr uint32_t kHistKeyBits = 14;     // LDS histogram cache key: row << 14 | bucket
 constexpr uint32_t kHistSlotsMax = 4096;  // LDS histogram cache slots (8 bytes each, 4-way sets)
 constexpr uint32_t kMedWaves = 4;         // median kernel: waves sharing one (window, site) item
@@ -604,6 +606,20 @@ __device__ __forceinline__ void load_addr(Addr<R> &t, const ClassifyArgs &a, uin
   }
 }
 
+// The lower 32 lanes of b and the upper 32 of a change places (every lane
+// active).
+__device__ __forceinline__ void swap_halves(u64x2 &a, u64x2 &b) {
+  u32x4 x = __builtin_bit_cast(u32x4, a), y = __builtin_bit_cast(u32x4, b);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const auto r = __builtin_amdgcn_permlane32_swap(x[j], y[j], false, false);
+    x[j] = r[0];
+    y[j] = r[1];
+  }
+  a = __builtin_bit_cast(u64x2, x);
+  b = __builtin_bit_cast(u64x2, y);
+}
+
 // The byte counts of 4 records take two loads of the same lines.  With the
 // non-temporal hint the first load's lines may go before the second reads
 // them: where lookups read trie nodes, whose misses take the same cache
@@ -612,7 +628,18 @@ __device__ __forceinline__ void load_addr(Addr<R> &t, const ClassifyArgs &a, uin
 // 102.0 against 95.6 us a call, 639 against 625 for 8 windows in one).  Without
 // nodes the hint is up to 1 % faster (256 windows on the 64-site registry,
 // 1,367 against 1,386 us).
-template <int R, bool VEC, int LAY>
+// LONG: each load takes whole lines (lanes l and l + 32 the two halves of 4
+// records of the one, then of the other) and the lanes then exchange halves,
+// with the hint, as lines are needed once: the nodes keep the L2.  With a table
+// beyond LDS, which goes with a large trie: 5 M records on 20,000 sites 125.2
+// -> 121.4 us, 100 M 1,443 -> 1,398.  Else from kLongRecords on: 8 windows of
+// 10 M records 627 -> 614, 20 M on 1,000 sites 175.2 -> 172.8, 16.8 M 149.8 ->
+// 148.3.  Shorter byte counts are partly still in the 256 MB memory cache, from
+// the kernel that wrote them or a call before, and the hint gives that up: 12 M
+// 111.4 and 112.9, 8 M 79.0 and 82.8, classified again among two others.  (With
+// histograms or per-host statistics nothing was gained; a branch between two
+// loops in one kernel spills registers: 1 % on every other call.)
+template <int R, bool VEC, int LAY, bool LONG>
 __device__ __forceinline__ void load_rest(Rest<R> &t, const ClassifyArgs &a, uint64_t base, uint64_t end) {
   // (lanes past the end load the range's last records, as in load_addr)
   if (VEC) {
@@ -620,7 +647,13 @@ __device__ __forceinline__ void load_rest(Rest<R> &t, const ClassifyArgs &a, uin
     const uint64_t at = idx < end ? idx : end - 4;
     const u32x4 pk = ldg_nt4(a.packets + at), f = ldg_nt4(a.first + at), l = ldg_nt4(a.last + at);
     u64x2 b0, b1;
-    if (LAY != kLinesOnly) {
+    if (LONG) {
+      const uint32_t lane = threadIdx.x % 64u;
+      const uint64_t i0 = base + 4u * (threadIdx.x - lane) + 4u * (lane % 32u) + 2u * (lane / 32u), i1 = i0 + 128u;
+      b0 = ldg_nt2(a.bytes + (i0 < end ? i0 : end - 2));
+      b1 = ldg_nt2(a.bytes + (i1 < end ? i1 : end - 2));
+      swap_halves(b0, b1);
+    } else if (LAY != kLinesOnly) {
       b0 = *(const u64x2_any *)(a.bytes + at);
       b1 = *(const u64x2_any *)(a.bytes + at + 2);
     } else {
@@ -826,11 +859,12 @@ template <int R, bool VEC, int LAY, bool ACC_LDS, uint32_t FEAT>
 __device__ __forceinline__ void process_range(const ClassifyArgs &a, const Lds &L, u64 *g_tab, uint32_t *h_tab,
                                               uint64_t lo, uint64_t hi) {
   constexpr uint64_t T = (uint64_t)kThreads * R;
+  constexpr bool LONG = VEC && (FEAT == kFeatLong || (FEAT == 0u && LAY == kNodes && !ACC_LDS));
   Addr<R> cur;
   load_addr<R, VEC>(cur, a, lo, hi);
   for (uint64_t base = lo; base < hi; base += T) {
     Rest<R> rest;
-    load_rest<R, VEC, LAY>(rest, a, base, hi);
+    load_rest<R, VEC, LAY, LONG>(rest, a, base, hi);
     Addr<R> nxt;
     load_addr<R, VEC>(nxt, a, base + T, hi);  // past the end: reloads the last records, marked invalid
     uint32_t row[R];
@@ -1371,7 +1405,7 @@ int device_cus(int dev) {
 
 typedef void (*KernelFn)(const ClassifyArgs);
 
-constexpr int kLayouts = 3, kShapes = 3, kVariants = 4 * kShapes * kLayouts * 2;
+constexpr int kLayouts = 3, kShapes = 3, kVariants = 5 * kShapes * kLayouts * 2;
 
 // variant slot: ((feat * kShapes + shape) * kLayouts + layout) * 2 + acc; shapes: R=1, R=2, R=4
 template <int R, bool V, uint32_t F>
@@ -1399,6 +1433,7 @@ KernelFn pick(int shape, int layout, bool acc, uint32_t feat) {
     case 0: return pick_shape<0>(shape, layout, acc);
     case kFeatHist: return pick_shape<kFeatHist>(shape, layout, acc);
     case kFeatHosts: return pick_shape<kFeatHosts>(shape, layout, acc);
+    case kFeatLong: return classify_kernel<4, true, kNodes, true, kFeatLong>;  // the one use
     default: return pick_shape<kFeatHist | kFeatHosts>(shape, layout, acc);
   }
 }
@@ -1704,9 +1739,19 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
   const uint32_t feat = (p.rate_hist ? kFeatHist : 0u) | (p.hosts ? kFeatHosts : 0u);
   const int layout = !reg->lines_in_lds ? kLinesGlobal : (reg->info.n_nodes ? kNodes : kLinesOnly);
   KernelFn fn = pick(shape, layout, reg->acc_in_lds, feat);
+  const auto allow = [&](KernelFn f, uint32_t ft) {
+    return allow_lds(f, (((int)ft * kShapes + shape) * kLayouts + layout) * 2 + (reg->acc_in_lds ? 1 : 0), dev);
+  };
   if (rec->n > 0) {
-    e = allow_lds(fn, (((int)feat * kShapes + shape) * kLayouts + layout) * 2 + (reg->acc_in_lds ? 1 : 0), dev);
+    e = allow(fn, feat);
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
+    if (feat == 0u && layout == kNodes && R == 4u && reg->acc_in_lds) {
+      // both variants of this call, whatever the length that came first
+      KernelFn lfn = pick(shape, layout, reg->acc_in_lds, kFeatLong);
+      e = allow(lfn, kFeatLong);
+      if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute");
+      if (rec->n >= kLongRecords) fn = lfn;
+    }
   }
   if (hist_work) {
     e = hist_prepare(dev);
