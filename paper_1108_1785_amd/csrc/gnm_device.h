@@ -13,6 +13,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr uint32_t kBuckets = 10001;  // rate histogram: 10 kbps buckets, the last for >= 100 Mbps
 constexpr uint32_t kBucketBps = 10000;
+constexpr uint32_t kXcds = 8;  // workgroups are dealt to these round robin; each has its own L2
 
 // First record of classify workgroup b's slice of n records on `grid`
 // workgroups: an even split cut at multiples of 4 records (slice `grid`

@@ -32,7 +32,6 @@ namespace gnm {
 constexpr uint32_t kPartThreads = 1024;  // count and scatter workgroups (16 waves: one per classify workgroup)
 constexpr uint32_t kPartScanWaves = 16;  // scan: waves sharing one group of 64 partitions
 constexpr uint32_t kPartScanKeep = 16;  // scan: counts per lane in flight
-constexpr uint32_t kXcds = 8;            // each with its own L2
 constexpr uint32_t kPartUnroll = 4;      // count and scatter: entries per lane in flight
 
 template <class E>
