@@ -289,10 +289,10 @@ uint64_t gnm_workspace_bytes(const gnm_registry *reg, uint32_t grid_blocks);
  * For one whose table does not (gnm_registry_info.acc_in_lds == 0), the
  * workspace holds the spilled rows instead: the rows that miss a workgroup's
  * LDS row cache and the cached rows flushed at window changes are staged as
- * 64-byte partial rows (at most one per record, and twice: staged, then in
- * partition order) and merged by one workgroup per (window, 256 table rows),
- * which writes its rows of the table and their flag bytes without
- * device-scope atomics: about 128 bytes per record.  Without that workspace
+ * 16-byte entries, by ranges of 256 table rows, and merged by one workgroup
+ * per (window, 256 table rows), which writes its rows of the table and their
+ * flag bytes without device-scope atomics: about 128 bytes per record, so
+ * that ranges of unequal use have room.  Without that workspace
  * the rows go to the table with device-scope atomics, with the same results.
  * 0 for a NULL registry, n_windows = 0, or more than 16,384 (window, 256-row)
  * ranges (such calls always use the atomics).

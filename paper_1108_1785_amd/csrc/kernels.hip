@@ -61,7 +61,8 @@ constexpr uint32_t kRedRows = 8;     // reduce kernel: table rows (4 sites) per 
 constexpr uint32_t kRedWords = kRedRows * kAccFields;  // reduce kernel: 56 table words, one per lane
 constexpr uint32_t kRedGroups = 16;  // reduce kernel: at most 16 waves, each summing every G-th slot
 constexpr uint32_t kRedUnroll = 8;   // reduce kernel: slot loads in flight per lane
-constexpr uint64_t kLongRecords = 1ull << 24;  // byte counts of half the memory cache
+constexpr uint64_t kMemoryCache = 256ull << 20;  // bytes of the cache between the L2s and HBM
+constexpr uint64_t kLongRecords = kMemoryCache / 16u;  // byte counts of half of it
 constexpr uint32_t kSmallTable = 16384;   // bytes of a table that costs a workgroup little to start and merge
 constexpr uint32_t kFeatHist = 1;         // classify_kernel FEAT bits: rate histograms,
 constexpr uint32_t kFeatHosts = 2;        //   per-host statistics,
@@ -1280,6 +1281,7 @@ __device__ __forceinline__ uint32_t row_median(const uint32_t *row, u64 bsum, u6
 // 64j + lane), streamed with coalesced loads, 32 in flight per lane.  The
 // last, partial batch is read as the row's final 1024 buckets (in bounds,
 // same immediate offsets) and counts only its own buckets.
+template <bool NT>
 __device__ __forceinline__ void batch_sums(const uint32_t *r0, const uint32_t *r1, uint32_t b, uint32_t lane,
                                            u64 &s0, u64 &s1) {
   const uint32_t lo = b * kMedBatchWords;
@@ -1288,8 +1290,8 @@ __device__ __forceinline__ void batch_sums(const uint32_t *r0, const uint32_t *r
   uint32_t v0[kMedRun], v1[kMedRun];
 #pragma unroll
   for (uint32_t j = 0; j < kMedRun; ++j) {
-    v0[j] = p0[j * 64u];
-    v1[j] = p1[j * 64u];
+    v0[j] = NT ? __builtin_nontemporal_load(p0 + j * 64u) : p0[j * 64u];
+    v1[j] = NT ? __builtin_nontemporal_load(p1 + j * 64u) : p1[j * 64u];
   }
   s0 = 0;
   s1 = 0;
@@ -1313,9 +1315,11 @@ __device__ __forceinline__ void batch_sums(const uint32_t *r0, const uint32_t *r
 // the window before.
 // Bound by reading 80 KB per item, and for few items by its chain of loads
 // and sums over lanes.  1,000 items just filled (80 MB): 17.9 us (4.5 TB/s);
-// 22.6 with non-temporal loads, which fetch rows that the caches still hold
-// (16,000 items: 284 us, non-temporal 347).  Both rows kept in registers by
+// 22.6 with non-temporal loads (NT), which fetch rows that the caches still
+// hold.  (The rows then take the classify kernel's trie nodes out of the L2,
+// which costs the next call up to 4 of these 5 us.)  Both rows kept in registers by
 // ten waves, nothing re-read: 26.5 (registers allow one workgroup per CU).
+template <bool NT>
 __global__ __launch_bounds__(64 * kMedBatches) void median_kernel(const uint32_t *__restrict__ hist, uint64_t items,
                                                                  uint64_t threshold, uint64_t need,
                                                                  uint32_t *__restrict__ median,
@@ -1330,7 +1334,7 @@ __global__ __launch_bounds__(64 * kMedBatches) void median_kernel(const uint32_t
 #pragma unroll 1
     for (uint32_t b = wave; b < kMedBatches; b += blockDim.x / 64u) {
       u64 s0, s1;
-      batch_sums(r0, r1, b, lane, s0, s1);
+      batch_sums<NT>(r0, r1, b, lane, s0, s1);
       s0 = wave_sum(s0);
       s1 = wave_sum(s1);
       if (lane == 0u) {
@@ -1909,7 +1913,12 @@ extern "C" int gnm_median_flags(const gnm_registry *reg, const uint32_t *rate_hi
   };
   const bool warn = n_windows == 1 &&
                     (!prev_flags || (apart(flags, items) && apart(median_bucket, items * 2u * sizeof(uint32_t))));
-  hipLaunchKernelGGL(median_kernel, dim3((uint32_t)(blocks < cap ? blocks : cap)), dim3(64u * waves), 0, stream,
+  // Histograms beyond the memory cache are no longer there from the kernel that
+  // wrote them.  Classify and medians of 10 M records on 1,000 sites, plain and
+  // non-temporal: 2 windows (160 MB) 200 and 211 us, 3 (240 MB) 247 and 255, 4
+  // (320 MB) 293 and 280; 80 M in 8 1,091 and 1,088.
+  const bool nt = items * 2u * kBuckets * sizeof(uint32_t) > kMemoryCache;
+  hipLaunchKernelGGL(nt ? median_kernel<true> : median_kernel<false>, dim3((uint32_t)(blocks < cap ? blocks : cap)), dim3(64u * waves), 0, stream,
                      rate_hist, items, threshold_bps, need, median_bucket, flags, warn ? prev_flags : nullptr);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "median launch");

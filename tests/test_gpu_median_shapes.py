@@ -48,8 +48,9 @@ def _expect(h, nw, S, threshold, need, prev):
     return med, oracle.median_flags(med.reshape(nw, 2 * S), n.reshape(nw, 2 * S), S, threshold, need, prev)
 
 
-# 64 sites: 64 items; 256 and 320, about the line; 1,000 sites: one window of 1,000 items
-@pytest.mark.parametrize("sites,nw", [(64, 1), (64, 4), (64, 5), (1000, 1)])
+# 64 sites: 64 items; 256 and 320, about the line; 1,000 sites: one window of
+# 1,000 items, and 4, whose histograms are larger than the memory cache
+@pytest.mark.parametrize("sites,nw", [(64, 1), (64, 4), (64, 5), (1000, 1), (1000, 4)])
 @pytest.mark.parametrize("prev_kind", ["none", "apart", "in flags", "in medians"])
 def test_median_shapes(sites, nw, prev_kind):
     import torch
