@@ -83,22 +83,6 @@ __global__ __launch_bounds__(kPartThreads) void part_count_kernel(const PartArgs
   for (uint32_t p = threadIdx.x; p < P; p += kPartThreads) row[p] = h[p];
 }
 
-// Classify workgroup whose share of a partition is the i-th: by XCD (b mod 8,
-// as workgroups are dealt), so that the scatter workgroups of an XCD fill
-// neighbouring entries and its L2 writes whole lines back: 1.4 M 16-byte
-// entries scattered in 24 us, in the order of b in 29; 4-byte keys 12.6 and
-// 13.2.
-__device__ __forceinline__ uint32_t part_source(uint32_t i, uint32_t grid) {
-  const uint32_t per = grid / kXcds, longer = (grid % kXcds) * (per + 1u);  // the first XCDs have one more
-  if (i < longer) return (i % (per + 1u)) * kXcds + i / (per + 1u);
-  const uint32_t j = i - longer;
-  return (j % per) * kXcds + grid % kXcds + j / per;
-}
-
-__device__ __forceinline__ uint32_t part_next_source(uint32_t b, uint32_t grid) {
-  return b + kXcds < grid ? b + kXcds : b % kXcds + 1u;
-}
-
 // Column prefix sums of the count matrix, in the order of part_source:
 // workgroup x owns partitions 64x .. 64x + 63 (lane j: partition 64x + j); its
 // 16 waves each take a sixteenth of the classify workgroups, sum their counts
