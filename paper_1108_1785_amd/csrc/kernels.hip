@@ -63,6 +63,7 @@ constexpr uint32_t kRedGroups = 16;  // reduce kernel: at most 16 waves, each su
 constexpr uint32_t kRedUnroll = 8;   // reduce kernel: slot loads in flight per lane
 constexpr uint64_t kMemoryCache = 256ull << 20;  // bytes of the cache between the L2s and HBM
 constexpr uint64_t kLongRecords = kMemoryCache / 16u;  // byte counts of half of it
+constexpr uint32_t kHotEntries = 128;     // spilled rows: a workgroup's entries below which a tile needs no sharing
 constexpr uint32_t kSmallTable = 16384;   // bytes of a table that costs a workgroup little to start and merge
 constexpr uint32_t kFeatHist = 1;         // classify_kernel FEAT bits: rate histograms,
 constexpr uint32_t kFeatHosts = 2;        //   per-host statistics,
@@ -116,7 +117,9 @@ struct ClassifyArgs {
   char *ts_entry;                     // spilled rows (a table beyond LDS, with a workspace; NULL: device
   uint32_t *ts_count;                 //   atomics): workgroup b's range starts kTableRangeBytes * (lo_b +
   uint32_t ts_extra, ts_tiles;        //   b * ts_extra) bytes in and has ts_tiles parts; counts [grid][ts_tiles]
-  uint32_t lds_off_tc;                //   LDS cursors of the parts
+  uint32_t ts_bits;                   //   log2 of a tile's rows
+  uint32_t *ts_hot;                   //   [ts_tiles]: entries of fuller parts and of chunks (NULL: no tile is shared)
+  uint32_t lds_off_tc;                //   LDS cursors of the parts and of the tiles' chunks
   uint32_t *ks_key;                   // staged histogram keys (FEAT & kFeatHist, with a workspace; NULL: the
   uint32_t *ks_count;                 //   LDS cache and device atomics): workgroup b's at [lo_b, lo_b + ks_count[b])
   uint32_t *kp_hist;                  // staged keys counted per partition here: [grid][kp_parts] (NULL: not here)
@@ -326,9 +329,11 @@ struct Lds {
   uint32_t hslots;  // histogram cache slots (0 = none)
   uint32_t *hcur;   // per-host staging: entries this workgroup has staged
   HostEntry *se;    // per-host staging: this workgroup's range
-  uint32_t *tcur;   // spilled rows: appends to each part of this workgroup's range
+  uint32_t *tcur;   // spilled rows: cursors of the parts, of the tiles' chunks; chunks taken
   TableEntry *te;   // spilled rows: this workgroup's range (NULL: misses and flushes use device atomics)
   uint32_t tcap;    // spilled rows: entries in a part
+  uint64_t trecs;   // spilled rows: records of the slice, and the range's extra room
+  uint32_t tbits, tiles;  // spilled rows: log2 of a tile's rows; tiles
   uint32_t *kcur;   // staged histogram keys: keys this workgroup has staged (without per-host staging)
   uint32_t *ke;     // staged histogram keys: this workgroup's range (NULL: the histogram cache)
   uint32_t *kp;     // staged histogram keys per partition (NULL: counted by the histogram kernels)
@@ -498,60 +503,233 @@ __device__ __forceinline__ void flush_hist(const Lds &L, uint32_t *h) {
   __syncthreads();
 }
 
-// Place of k entries in the part of row's tile (beyond L.tcap: no room; a full
-// part's cursor is left alone, so that it cannot wrap).
-__device__ __forceinline__ uint32_t append_rows(const Lds &L, uint32_t row, uint32_t k) {
-  uint32_t *cur = &L.tcur[row / kTableTileRows];
-  return *(volatile uint32_t *)cur < L.tcap ? atomicAdd(cur, k) : L.tcap;
+// One staged entry of window `win`.
+__device__ __forceinline__ void put_entry(TableEntry *at, uint32_t row, uint32_t tbits, uint32_t win, uint32_t kind,
+                                          u64 x, u64 bytes) {
+  typedef u64 u64x2_ __attribute__((ext_vector_type(2)));
+  const uint32_t head = (((win << kEntKindBits) | kind) << tbits | (row & ((1u << tbits) - 1u))) << (kEntRowShift - 32u);
+  *(u64x2_ *)at = u64x2_{x, bytes | ((u64)head << 32)};
+}
+__device__ __forceinline__ void stage_entry(const Lds &L, uint32_t row, TableEntry *at, uint32_t kind, u64 x, u64 bytes) {
+  put_entry(at, row, L.tbits, L.win, kind, x, bytes);
 }
 
-// One staged entry of window L.win at place `pos` of its part.
-__device__ __forceinline__ void stage_entry(const Lds &L, uint32_t row, uint32_t pos, uint32_t kind, u64 x, u64 bytes) {
-  typedef u64 u64x2_ __attribute__((ext_vector_type(2)));
-  const uint32_t head =
-      (L.win << (kEntWindowShift - 32u)) | (kind << (kEntKindShift - 32u)) | ((row % kTableTileRows) << (kEntRowShift - 32u));
-  *(u64x2_ *)(L.te + (uint64_t)(row / kTableTileRows) * L.tcap + pos) = u64x2_{x, bytes | ((u64)head << 32)};
+// Places for k entries of row, one after the other, in its tile's part; NULL
+// when they are not there.  (A full part's cursor is left alone, so that it
+// cannot wrap; places at the end that are too few get entries that add nothing.)
+__device__ __forceinline__ TableEntry *part_places(const Lds &L, uint32_t row, uint32_t k) {
+  const uint32_t tile = row >> L.tbits;
+  uint32_t *cur = &L.tcur[tile];
+  if (*(volatile uint32_t *)cur >= L.tcap) return nullptr;
+  uint32_t v = atomicAdd(cur, k);
+  TableEntry *part = L.te + (uint64_t)tile * L.tcap;
+  if (v + k <= L.tcap) return part + v;
+  for (; v < L.tcap; ++v) stage_entry(L, row, part + v, kRowRateMax, 0ull, 0ull);
+  return nullptr;
+}
+
+// The chunks of a workgroup's range, worked out where they are used: few
+// calls do, and the record loop has no registers left for their layout.  A
+// tile's chunk cursor is 0, or kTableMore, its present chunk and the entries
+// taken of it (more than there are when it is full: at most the 7 of every lane
+// that saw it just before).
+struct Chunks {
+  uint32_t *cur, *taken;  // LDS: chunk cursors of the tiles; chunks taken
+  TableChunk *meta;
+  TableEntry *entries;
+  uint32_t bits, chunks, win;
+};
+static_assert((1u << kChunkBitsMax) + 7u * kThreads < (1u << kUsedBits), "a chunk cursor's count cannot run over");
+
+__device__ __forceinline__ Chunks chunks_of(uint32_t *tcur, TableEntry *te, const TableRange &r, uint32_t tiles,
+                                            uint32_t win) {
+  return Chunks{tcur + tiles, tcur + 2u * tiles, (TableChunk *)((char *)te + r.meta),
+                (TableEntry *)((char *)te + r.entries()), r.bits, r.chunks, win};
+}
+
+// Place of a chunk cursor's value; NULL where its chunk is full or there is none.
+__device__ __forceinline__ TableEntry *chunk_place(const Chunks &c, uint32_t v) {
+  const uint32_t used = v & ((1u << kUsedBits) - 1u);
+  if (!(v & kTableMore) || used >> c.bits) return nullptr;
+  return c.entries + ((uint64_t)((v & ~kTableMore) >> kUsedBits) << c.bits) + used;
+}
+
+// The count of a chunk that is no longer a tile's present one (v: the cursor),
+// and the window that it may have entries of at most.
+__device__ __forceinline__ void close_chunk(const Chunks &c, uint32_t v) {
+  if (!(v & kTableMore)) return;
+  const uint32_t used = v & ((1u << kUsedBits) - 1u), C = 1u << c.bits;
+  TableChunk *m = c.meta + ((v & ~kTableMore) >> kUsedBits);
+  m->count = used < C ? used : C;
+  m->last = c.win;
+}
+
+// Places for k entries (0 to 7) of each lane's row, one after the other, in its
+// tile's chunks; NULL when the chunks are used up (or k is 0).  The lanes of the
+// wave that find a tile's present chunk full take new ones for it, and the last
+// of them becomes the present one in a single exchange, whatever other waves
+// have put there meanwhile (what is left of theirs stays empty): nothing waits
+// for another wave.  (A call, which works the layout out again: inlined, its
+// registers would make the record loop's spill, and a kernel with scratch memory
+// starts 2 us later.)
+static __device__ __noinline__ TableEntry *take_chunks(uint32_t *tcur, TableEntry *te, uint64_t trecs, uint32_t tiles,
+                                                       uint32_t tbits, uint32_t win, uint32_t row, uint32_t k) {
+  const Chunks c = chunks_of(tcur, te, table_range(trecs, 0u, tiles), tiles, win);
+  const uint32_t C = 1u << c.bits, lane = __lane_id(), tile = row >> tbits;
+  TableEntry *at = nullptr;
+  while (__builtin_amdgcn_ballot_w64(k != 0u)) {
+    if (k && chunk_place(c, *(volatile uint32_t *)&c.cur[tile])) {
+      const uint32_t v = atomicAdd(&c.cur[tile], k);
+      TableEntry *first = chunk_place(c, v);
+      if (chunk_place(c, v + k - 1u)) {
+        at = first;
+        k = 0u;
+      } else if (first) {  // too few
+        const uint32_t left = C - (v & ((1u << kUsedBits) - 1u));
+        for (uint32_t j = 0; j < left; ++j) put_entry(first + j, row, tbits, win, kRowRateMax, 0ull, 0ull);
+      }
+    }
+    const uint64_t open = __builtin_amdgcn_ballot_w64(k != 0u);
+    if (open == 0ull) break;
+    const uint32_t leader = (uint32_t)__builtin_ctzll(open);
+    const uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)tile, leader);
+    // the lanes of tile t: places before each lane's, and of all of them
+    const bool same = k && tile == t;
+    uint32_t before = 0, m = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < 3u; ++j) {
+      const uint64_t bit = __builtin_amdgcn_ballot_w64(same && ((k >> j) & 1u));
+      before += (uint32_t)__builtin_popcountll(bit & ((1ull << lane) - 1ull)) << j;
+      m += (uint32_t)__builtin_popcountll(bit) << j;
+    }
+    const uint32_t q = (m + C - 1u) >> c.bits;
+    uint32_t n = c.chunks;
+    if (lane == leader && *(volatile uint32_t *)c.taken < c.chunks) n = atomicAdd(c.taken, q);
+    n = (uint32_t)__builtin_amdgcn_readlane((int)n, leader);
+    if (n + q <= c.chunks) {
+      if (same) at = c.entries + ((uint64_t)n << c.bits) + before;
+      // (the last chunk's count and last window come when it is closed)
+      for (uint32_t i = lane; i < q; i += 64u) {
+        c.meta[n + i].id = t;
+        c.meta[n + i].first = c.win;
+        if (i + 1u < q) {
+          c.meta[n + i].count = C;
+          c.meta[n + i].last = c.win;
+        }
+      }
+      if (lane == leader)
+        close_chunk(c, atomicExch(&c.cur[t], kTableMore | (n + q - 1u) << kUsedBits | (m - ((q - 1u) << c.bits))));
+    } else if (n < c.chunks && lane == leader) {
+      for (; n < c.chunks; ++n) c.meta[n] = TableChunk{t, c.win, 0u, c.win};  // too few: taken, and left empty
+    }
+    if (same) k = 0u;
+  }
+  return at;
 }
 
 // Flush the LDS cache slots into window table g with device-scope atomics,
-// or, when the table spills and the row's part has room, as staged entries;
-// then free them.
+// or, when the table spills, as staged entries; then free them.
 __device__ __forceinline__ void flush_cache(const Lds &L, u64 *__restrict__ g) {
-  __syncthreads();
-  for (uint32_t sl = threadIdx.x; sl < L.slots; sl += kThreads) {
-    const uint32_t tag = L.tags[sl];
-    if (tag == 0u) continue;
+  // a slot's row to its 4 (with bulk flows 7) staged entries, or to the table
+  auto send = [&](uint32_t sl, uint32_t row, TableEntry *at) {
     u64 *t = L.acc + sl * kAccFields;
-    const uint32_t row = tag - 1u;
     const u64 cnt = t[kCnt], nb = cnt >> 32;
-    bool staged = false;
-    if (L.te) {
-      const uint32_t k = nb ? 7u : 4u, pos = append_rows(L, row, k);
-      staged = pos + k <= L.tcap;
-      if (staged) {
-        stage_entry(L, row, pos, kRowCnt, cnt, 0ull);
-        stage_entry(L, row, pos + 1u, kRowBytes, t[kBytes], 0ull);
-        stage_entry(L, row, pos + 2u, kRowPackets, t[kPackets], 0ull);
-        stage_entry(L, row, pos + 3u, kRowDur, t[kDur], 0ull);
-        if (nb) {
-          stage_entry(L, row, pos + 4u, kRowRateSum, t[kRateSum], 0ull);
-          stage_entry(L, row, pos + 5u, kRowRateMin, t[kRateMin], 0ull);
-          stage_entry(L, row, pos + 6u, kRowRateMax, t[kRateMax], 0ull);
-        }
-      } else {
-        // the last places of a full part: entries that add nothing
-        for (uint32_t p = pos; p < L.tcap; ++p) stage_entry(L, row, p, kRowRateMax, 0ull, 0ull);
+    if (at) {
+      stage_entry(L, row, at, kRowCnt, cnt, 0ull);
+      stage_entry(L, row, at + 1, kRowBytes, t[kBytes], 0ull);
+      stage_entry(L, row, at + 2, kRowPackets, t[kPackets], 0ull);
+      stage_entry(L, row, at + 3, kRowDur, t[kDur], 0ull);
+      if (nb) {
+        stage_entry(L, row, at + 4, kRowRateSum, t[kRateSum], 0ull);
+        stage_entry(L, row, at + 5, kRowRateMin, t[kRateMin], 0ull);
+        stage_entry(L, row, at + 6, kRowRateMax, t[kRateMax], 0ull);
       }
-    }
-    if (!staged) {
+    } else {
       add_device(g, row, cnt & 0xFFFFFFFFull, t[kBytes], t[kPackets], t[kDur]);
       if (nb) add_device_rate(g, row, nb, t[kRateSum], t[kRateMin], t[kRateMax]);
     }
     t[kCnt] = t[kBytes] = t[kPackets] = t[kDur] = t[kRateSum] = t[kRateMax] = 0;
     t[kRateMin] = ~0ull;
     L.tags[sl] = 0u;
+  };
+  auto entries_of = [&](uint32_t sl) { return L.acc[sl * kAccFields + kCnt] >> 32 ? 7u : 4u; };
+  __syncthreads();
+  bool left = false;  // rows whose tile's part was full stay for a second pass
+  for (uint32_t sl = threadIdx.x; sl < L.slots; sl += kThreads) {
+    const uint32_t tag = L.tags[sl];
+    if (tag == 0u) continue;
+    TableEntry *at = L.te ? part_places(L, tag - 1u, entries_of(sl)) : nullptr;
+    if (at || !L.te) send(sl, tag - 1u, at);
+    else left = true;
+  }
+  if (__builtin_amdgcn_ballot_w64(left)) {
+    for (uint32_t s0 = 0; s0 < L.slots; s0 += kThreads) {
+      const uint32_t sl = s0 + threadIdx.x, tag = sl < L.slots ? L.tags[sl] : 0u;
+      TableEntry *at = take_chunks(L.tcur, L.te, L.trecs, L.tiles, L.tbits, L.win, tag ? tag - 1u : 0u,
+                                   tag ? entries_of(sl) : 0u);
+      if (tag) send(sl, tag - 1u, at);
+    }
   }
   __syncthreads();
+}
+
+// After a workgroup's last entry and a barrier: the parts' counts, the entries
+// of fuller tiles, and, where tiles have taken chunks, the chunks listed by tile
+// for the merge.
+__device__ __forceinline__ void publish_parts(const Lds &L, uint32_t *count, uint32_t *hot) {
+  const uint32_t tid = threadIdx.x, tiles = L.tiles, cap = L.tcap;
+  uint32_t *n = L.tcur + tiles;  // chunk cursors
+  const bool any = n[tiles] != 0u;
+  // a tile of v entries, where they are more than half a part
+  auto fuller = [&](uint32_t j, uint32_t v) {
+    if (hot && 2u * v > cap && v >= kHotEntries)
+      __hip_atomic_fetch_add(&hot[j], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  for (uint32_t j = tid; j < tiles; j += kThreads) {
+    const uint32_t v = L.tcur[j] < cap ? L.tcur[j] : cap;
+    count[j] = v | (n[j] & kTableMore);
+    if (!any) fuller(j, v);
+  }
+  if (!any) return;
+  // chunks and entries of each tile
+  const TableRange tr = table_range(L.trecs, 0u, tiles);
+  const Chunks ch = chunks_of(L.tcur, L.te, tr, tiles, L.win);
+  const uint32_t taken = *ch.taken < ch.chunks ? *ch.taken : ch.chunks;
+  for (uint32_t j = tid; j < tiles; j += kThreads) close_chunk(ch, n[j]);
+  __syncthreads();
+  for (uint32_t j = tid; j < tiles; j += kThreads) {
+    L.tcur[j] = L.tcur[j] < cap ? L.tcur[j] : cap;
+    n[j] = 0u;
+  }
+  __syncthreads();
+  for (uint32_t c = tid; c < taken; c += kThreads) {
+    atomicAdd(&L.tcur[ch.meta[c].id], ch.meta[c].count);
+    atomicAdd(&n[ch.meta[c].id], 1u);
+  }
+  __syncthreads();
+  uint32_t *first = (uint32_t *)((char *)L.te + tr.first);
+  if (tid < 64u) {  // exclusive sums, by one wave
+    uint32_t run = 0;
+    for (uint32_t j0 = 0; j0 < tiles; j0 += 64u) {
+      const uint32_t j = j0 + tid, c = j < tiles ? n[j] : 0u;
+      uint32_t x = c;
+#pragma unroll
+      for (uint32_t o = 1; o < 64u; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, 64);
+        if (tid >= o) x += y;
+      }
+      if (j < tiles) n[j] = first[j] = run + x - c;
+      run += __shfl(x, 63, 64);
+    }
+    if (tid == 0u) first[tiles] = run;
+  }
+  for (uint32_t j = tid; j < tiles; j += kThreads) fuller(j, L.tcur[j]);
+  __syncthreads();
+  TableChunk *list = (TableChunk *)((char *)L.te + tr.list());
+  for (uint32_t c = tid; c < taken; c += kThreads) {
+    const TableChunk m = ch.meta[c];
+    list[atomicAdd(&n[m.id], 1u)] = TableChunk{c, m.first, m.count, m.last};
+  }
 }
 
 // Copy the workgroup's LDS table (same row layout) to its workspace slot and
@@ -797,6 +975,7 @@ __device__ __forceinline__ void aggregate_tile(const Addr<R> &t, const uint32_t 
     hpos = reserve_hosts<R>(HOSTS ? L.hcur : L.kcur, want, hb);
   }
   const uint64_t below = (1ull << __lane_id()) - 1ull;
+  uint32_t over = 0;  // bit k: record k is left for a chunk of its tile
 #pragma unroll
   for (int k = 0; k < R; ++k) {
     const uint32_t dur = durv[k];
@@ -805,15 +984,20 @@ __device__ __forceinline__ void aggregate_tile(const Addr<R> &t, const uint32_t 
     // (a spare LDS row for invalid records instead of this branch measured
     // 10 % slower on the 64-site registry)
     if (valid[k]) code = accumulate<ACC_LDS>(L, g_tab, row[k], r.b[k], r.pk[k], dur, bulk);
-    // a spilled table: a record that missed the cache is staged, or added to
-    // the device table where its part is full
+    // a spilled table: a record that missed the cache is staged in its tile's
+    // part, or, when that is full, below (one whose bytes an entry does not
+    // hold is added to the device table)
     bool staged = false;
     if (!ACC_LDS && L.te != nullptr) {
       if (valid[k] && !(code & kInSlot)) {
-        const uint32_t pos = (r.b[k] >> kEntBytesBits) == 0u ? append_rows(L, row[k], 1u) : L.tcap;
-        staged = pos < L.tcap;
-        if (staged) stage_entry(L, row[k], pos, kRec, (u64)r.pk[k] | ((u64)dur << 32), r.b[k]);
-        else add_device(g_tab, row[k], 1ull, r.b[k], r.pk[k], dur);
+        staged = (r.b[k] >> kEntBytesBits) == 0u;
+        if (staged) {
+          TableEntry *place = part_places(L, row[k], 1u);
+          if (place) stage_entry(L, row[k], place, kRec, (u64)r.pk[k] | ((u64)dur << 32), r.b[k]);
+          else over |= 1u << k;
+        } else {
+          add_device(g_tab, row[k], 1ull, r.b[k], r.pk[k], dur);
+        }
       }
     }
     uint64_t rate = 0;
@@ -840,6 +1024,35 @@ __device__ __forceinline__ void aggregate_tile(const Addr<R> &t, const uint32_t 
       }
     }
     if (HOSTS || kst) hpos += (uint32_t)__builtin_popcountll(hb[k]);
+  }
+  // Records whose tile's part was full, one per lane and turn: staged in a chunk
+  // or, when those are used up, added to the device table.  (Read again: kept in
+  // registers until here they would spill some.)
+  while (!ACC_LDS && __builtin_amdgcn_ballot_w64(over != 0u)) {
+    uint32_t rw = 0;
+    int which = 0;
+#pragma unroll
+    for (int k = R - 1; k >= 0; --k) {
+      if ((over >> k) & 1u) {
+        rw = row[k];
+        which = k;
+      }
+    }
+    TableEntry *place = take_chunks(L.tcur, L.te, L.trecs, L.tiles, L.tbits, L.win, rw, over ? 1u : 0u);
+    if (over == 0u) continue;
+    over &= over - 1u;
+    const uint64_t i = at(which), b = a.bytes[i];
+    const uint32_t pk = a.packets[i], dur = a.last[i] - a.first[i];
+    if (place) {
+      stage_entry(L, rw, place, kRec, (u64)pk | ((u64)dur << 32), b);
+    } else {
+      add_device(g_tab, rw, 1ull, b, pk, dur);
+      if (b > a.bulk_bytes && dur != 0u && b >= (uint64_t)a.min_avg_packet_bytes * pk && pk >= a.min_packets &&
+          dur >= a.min_duration_ms) {
+        const uint64_t rate = rate_bps(b, dur);
+        add_device_rate(g_tab, rw, 1ull, rate, rate, rate);
+      }
+    }
   }
 }
 
@@ -879,8 +1092,10 @@ __device__ __forceinline__ void process_range(const ClassifyArgs &a, const Lds &
 
 // ---------------------------------------------------------------- kernels
 
-__global__ void init_acc_kernel(u64 *__restrict__ acc, uint64_t words) {
+// The initial table; `zeros` words at `zero` cleared.
+__global__ void init_acc_kernel(u64 *__restrict__ acc, uint64_t words, uint32_t *__restrict__ zero, uint64_t zeros) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < zeros) zero[i] = 0u;
   if (i < words) acc[i] = ((i & 7u) == 6u) ? ~0ull : 0ull;
 }
 
@@ -949,7 +1164,7 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const ClassifyArgs a
   if ((HOSTS || kst) && tid < 2u) s_hcur[tid] = 0u;
   uint32_t *s_tcur = (uint32_t *)(lds + a.lds_off_tc);
   if (spill)
-    for (uint32_t i = tid; i < a.ts_tiles; i += kThreads) s_tcur[i] = 0u;
+    for (uint32_t i = tid; i <= 2u * a.ts_tiles; i += kThreads) s_tcur[i] = 0u;
   uint32_t *s_kp = (uint32_t *)(lds + a.lds_off_kp);
   const bool kcount = kst && a.kp_hist != nullptr;
   if (kcount) {
@@ -970,7 +1185,8 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const ClassifyArgs a
   Lds L{s_root, s_lines, s_acc, s_tags, slots, s_htags, s_htags + hslots, hslots, s_hcur,
         HOSTS ? a.hs_entry + lo : nullptr, s_tcur,
         spill ? (TableEntry *)(a.ts_entry + kTableRangeBytes * (lo + (uint64_t)blockIdx.x * a.ts_extra)) : nullptr,
-        spill ? table_part_cap(hi - lo, a.ts_extra, a.ts_tiles) : 0u,
+        spill ? (uint32_t)__builtin_amdgcn_readfirstlane(table_range(hi - lo, a.ts_extra, a.ts_tiles).cap) : 0u,
+        hi - lo + a.ts_extra, a.ts_bits, a.ts_tiles,
         s_kcur, kst ? a.ks_key + lo : nullptr, kcount ? s_kp : nullptr, a.kp_shift, hcount ? s_hp : nullptr, a.hp_bits,
         0u, 0u};
   if (lo == hi) {
@@ -1031,9 +1247,7 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(const ClassifyArgs a
   if (HOSTS || spill || kst) {
     __syncthreads();
     if (HOSTS && tid == 0) a.hs_count[blockIdx.x] = *s_hcur;
-    if (spill)
-      for (uint32_t j = tid; j < a.ts_tiles; j += kThreads)
-        a.ts_count[(uint64_t)blockIdx.x * a.ts_tiles + j] = s_tcur[j] < L.tcap ? s_tcur[j] : L.tcap;
+    if (spill) publish_parts(L, a.ts_count + (uint64_t)blockIdx.x * a.ts_tiles, a.ts_hot);
     // with per-host staging the keys share its cursor
     if (kst && tid == 0) a.ks_count[blockIdx.x] = HOSTS ? *s_hcur : *s_kcur;
     if (kcount)
@@ -1640,26 +1854,39 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
   bool spill = !reg->acc_in_lds && rec->n > 0 && rec->n < (1ull << 32) && p.workspace &&
                ((uintptr_t)p.workspace & 255u) == 0 && table_fits(n_windows, (uint32_t)rows) &&
                p.workspace_bytes >= table_spill_bytes(rec->n, grid, n_windows, (uint32_t)rows, reg->cache_slots);
+  uint32_t tile_bits = table_tile_bits((uint32_t)rows);
+  TableStage ts{};
   if (spill) {
-    const uint32_t tiles = table_tiles((uint32_t)rows), need = 4u * tiles;
     constexpr uint32_t kSlotBytes = 8u * kAccFields + 4u;
     const uint32_t end = (lds_launch + 15u) & ~15u, cache = reg->cache_slots * kSlotBytes;
-    if (end + need <= lds_budget) {
-      a.lds_off_tc = end;
-      lds_launch = end + need;
-    } else if (cache >= need + 16u) {
-      a.cache_slots = ((cache - need - 16u) / kSlotBytes) & ~3u;
-      a.lds_off_tc = (reg->lds_off_acc + a.cache_slots * kSlotBytes + 15u) & ~15u;
-    } else {
-      spill = false;
+    for (;; ++tile_bits) {
+      const uint32_t need = 4u * (2u * table_tiles((uint32_t)rows, tile_bits) + 1u);
+      if (end + need <= lds_budget) {
+        a.lds_off_tc = end;
+        lds_launch = end + need;
+        break;
+      }
+      if (cache >= need + 16u) {
+        a.cache_slots = ((cache - need - 16u) / kSlotBytes) & ~3u;
+        a.lds_off_tc = (reg->lds_off_acc + a.cache_slots * kSlotBytes + 15u) & ~15u;
+        break;
+      }
+      if (tile_bits == kTileBitsMax) {
+        spill = false;
+        break;
+      }
     }
   }
   if (spill) {
-    const TableStage ts = table_stage(p.workspace, rec->n, grid, (uint32_t)rows, reg->cache_slots);
+    e = table_prepare(dev);
+    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute (table)");
+    a.ts_tiles = table_tiles((uint32_t)rows, tile_bits);
+    ts = table_stage(p.workspace, rec->n, grid, n_windows, a.ts_tiles, reg->cache_slots);
     a.ts_entry = ts.entry;
     a.ts_count = ts.count;
+    a.ts_hot = ts.more ? ts.hot : nullptr;
     a.ts_extra = (uint32_t)table_extra(reg->cache_slots);
-    a.ts_tiles = table_tiles((uint32_t)rows);
+    a.ts_bits = tile_bits;
   }
   // histograms with a workspace that also holds their keys, after what the
   // tables use of it: staged keys and the histogram kernels instead of the
@@ -1756,10 +1983,11 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
   }
   if (!launch) return GNM_OK;
 
-  if (!(p.flags & GNM_ACCUMULATE) && !overwrite) {
-    const uint64_t words = (uint64_t)n_windows * rows * 8u;
-    const uint64_t blocks = (words + 255) / 256;
-    hipLaunchKernelGGL(init_acc_kernel, dim3((uint32_t)blocks), dim3(256), 0, stream, (u64 *)acc, words);
+  if ((!(p.flags & GNM_ACCUMULATE) && !overwrite) || ts.words) {
+    const uint64_t words = p.flags & GNM_ACCUMULATE ? 0u : (uint64_t)n_windows * rows * 8u;
+    const uint64_t blocks = ((words > ts.words ? words : ts.words) + 255) / 256;
+    hipLaunchKernelGGL(init_acc_kernel, dim3((uint32_t)blocks), dim3(256), 0, stream, (u64 *)acc, words, ts.hot,
+                       (uint64_t)ts.words);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "init launch");
   }
@@ -1797,7 +2025,7 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
   if (spill) {
     const TableFlags tf{fl.flags, fl.threshold, fl.need, fl.n_sites};
     const BulkRule bulk{p.bulk_bytes, p.min_avg_packet_bytes, p.min_packets, p.min_duration_ms};
-    const int rc = table_merge_launch(p.workspace, rec->n, grid, window_offsets, n_windows, (uint32_t)rows,
+    const int rc = table_merge_launch(p.workspace, rec->n, grid, window_offsets, n_windows, (uint32_t)rows, tile_bits,
                                       reg->cache_slots, bulk, (unsigned long long *)acc, tf, stream);
     if (rc != GNM_OK) return rc;
   } else if (use_ws) {
