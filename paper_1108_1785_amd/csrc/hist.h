@@ -42,8 +42,29 @@ uint64_t hist_work_bytes(uint64_t n, uint64_t grid, uint32_t n_windows, uint32_t
 HistStage hist_stage(void *work, uint64_t n, uint64_t grid, uint32_t n_windows, uint32_t hist_rows);
 
 // Whether such a call counts its histograms straight from the staged keys, in
-// one kernel without partitions (and so without partition counts).
-bool hist_direct(uint64_t n, uint64_t grid, uint32_t n_windows, uint32_t hist_rows);
+// one kernel without partitions (and so without partition counts), at most:
+constexpr uint32_t kDirectGrid = 2048;            // classify workgroups (their ranges are held in LDS)
+constexpr uint64_t kDirectRecords = 100u << 10;   // records
+constexpr uint64_t kDirectWork = 1ull << 25;      // records x rows
+constexpr uint32_t kDirectAddRows = 2560;         // rows, of a call that accumulates
+// Three launches cost more than reading every key once per row, up to the
+// lines below (classify call and medians, with the partition kernels and with
+// hist_direct_kernel).  Records x rows: 16,384 on 2,000 rows 55.6 and 51.4 us,
+// 65,536 on 512 rows 42.0 and 37.8, but 30,000 on 2,000 rows 55.8 and 53.9 and
+// 100,000 57.5 and 70.9.  Records: what one row's workgroup may have to count;
+// 100,000 flows that are all bulk (classify call alone) take as long either
+// way, spread over 64 sites (26.0 and 26.0) or in one row (68.2 and 67.0),
+// 131,072 more (26.3 and 28.6, 65.3 and 77.0).
+// A call that accumulates writes only the rows that its flows are in: the
+// partition kernels pass over empty partitions, a workgroup per row has to read
+// the keys first.  2,000 rows (partition kernels, direct) 26.5 and 22.8 us for
+// 1,000 records, 32.6 and 29.6 for 16,000; 2,800 rows 33.4 and 33.0, 41.4 and
+// 42.1 (11,000); 4,000 rows 37.4 and 38.8, 46.5 and 50.0 (8,000); 64,000 rows
+// 214 and 440 (500 records).
+inline bool hist_direct(uint64_t n, uint64_t grid, uint32_t n_windows, uint32_t hist_rows, bool accumulate) {
+  const uint64_t rows = (uint64_t)n_windows * hist_rows;
+  return grid <= kDirectGrid && n <= kDirectRecords && n * rows <= kDirectWork && (!accumulate || rows <= kDirectAddRows);
+}
 
 // Kernel attributes of the histogram kernels on device dev (once per device,
 // outside any graph capture).

@@ -49,11 +49,8 @@ constexpr uint32_t kPartsTarget = 4096;   // partitions above which 2 (then 4) r
 constexpr uint32_t kOwnerPartBits = 14;   // overflow slice owner: slice << 14 | partition (< 16,384)
 constexpr uint32_t kBucketMask = (1u << kHistBucketBits) - 1u;
 
-// Small calls count straight from the staged keys (hist_direct_kernel), at most:
+// Small calls count straight from the staged keys (hist_direct_kernel).
 constexpr uint32_t kDirectThreads = 1024;
-constexpr uint32_t kDirectGrid = 2048;            // classify workgroups (their ranges are held in LDS)
-constexpr uint64_t kDirectRecords = 100u << 10;   // records
-constexpr uint64_t kDirectWork = 1ull << 25;      // records x rows
 constexpr uint32_t kDirectWideRows = 256;         // up to a row per CU: pieces of 2048 keys, else 1024
 constexpr int kDirectDense = 32;                  // lanes with keys of the row that are looked at for equal ones
 constexpr uint32_t kDirectRowWords = (3u + kBuckets + 3u) / 4u * 4u;
@@ -379,19 +376,6 @@ uint64_t hist_work_bytes(uint64_t n, uint64_t grid, uint32_t n_windows, uint32_t
   return layout(n, grid, plan(n, n_windows, hist_rows)).end;
 }
 
-// Three launches cost more than reading every key once per row, up to the
-// lines below (classify call and medians, with the partition kernels and with
-// hist_direct_kernel).  Records x rows: 16,384 on 2,000 rows 55.6 and 51.4 us,
-// 65,536 on 512 rows 42.0 and 37.8, but 30,000 on 2,000 rows 55.8 and 53.9 and
-// 100,000 57.5 and 70.9.  Records: what one row's workgroup may have to count;
-// 100,000 flows that are all bulk (classify call alone) take as long either
-// way, spread over 64 sites (26.0 and 26.0) or in one row (68.2 and 67.0),
-// 131,072 more (26.3 and 28.6, 65.3 and 77.0).
-bool hist_direct(uint64_t n, uint64_t grid, uint32_t n_windows, uint32_t hist_rows) {
-  const uint64_t rows = (uint64_t)n_windows * hist_rows;
-  return grid <= kDirectGrid && n <= kDirectRecords && n * rows <= kDirectWork;
-}
-
 HistStage hist_stage(void *work, uint64_t n, uint64_t grid, uint32_t n_windows, uint32_t hist_rows) {
   const Plan pl = plan(n, n_windows, hist_rows);
   const Layout L = layout(n, grid, pl);
@@ -422,7 +406,7 @@ int hist_pipeline_launch(void *work, uint64_t n, uint64_t grid, uint32_t n_windo
   const Plan pl = plan(n, n_windows, hist_rows);
   const Layout L = layout(n, grid, pl);
   char *w = (char *)work;
-  if (hist_direct(n, grid, n_windows, hist_rows)) {
+  if (hist_direct(n, grid, n_windows, hist_rows, accumulate)) {
     Direct d{};
     d.key = (const uint32_t *)(w + L.part.stage);
     d.count = (const uint32_t *)(w + L.part.scount);

@@ -1916,7 +1916,7 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
     a.hist_slots = hs;
     lds_launch = off + hs * 8u;
   }
-  if (hist_work && !hist_direct(rec->n, grid, n_windows, a.hist_rows)) {
+  if (hist_work && !hist_direct(rec->n, grid, n_windows, a.hist_rows, (p.flags & GNM_ACCUMULATE) != 0u)) {
     // the keys' partition counts in LDS too, when they fit that budget
     // (otherwise the count kernel counts them)
     const uint32_t off = (lds_launch + 15u) & ~15u;
