@@ -1677,13 +1677,23 @@ bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 // 16 waves whatever its LDS, and a second one per CU only starts when the
 // first ends: 10 M records on 64 sites 76.1 us with 512 workgroups, 67.0 with
 // 256; 3 M 38.3 and 30.1, 50 M in 256 windows 303 and 294.
-uint64_t launch_grid(const gnm_registry *reg, uint64_t n, uint32_t R, uint32_t grid_blocks, int dev) {
-  const uint64_t resident = (uint64_t)device_cus(dev) * (R == 4u ? 1u : blocks_per_cu(reg));
+uint64_t launch_grid(uint64_t n, uint32_t R, uint32_t grid_blocks, uint64_t resident) {
   const uint64_t tiles = (n + (uint64_t)kThreads * R - 1) / ((uint64_t)kThreads * R);
   uint64_t grid = grid_blocks ? grid_blocks : (tiles < resident ? tiles : resident);
   if (grid == 0) grid = 1;
   if (grid > 65535u * 16u) grid = 65535u * 16u;
   return grid;
+}
+
+uint64_t launch_grid(const gnm_registry *reg, uint64_t n, uint32_t R, uint32_t grid_blocks, int dev) {
+  return launch_grid(n, R, grid_blocks, (uint64_t)device_cus(dev) * (R == 4u ? 1u : blocks_per_cu(reg)));
+}
+
+// Workgroups that a call's work areas must have room for, whatever number it
+// starts: as many per CU as LDS allows.  Host buffers and the static scratch
+// that hold fewer are refused.
+uint64_t sized_grid(const gnm_registry *reg, uint64_t n, uint32_t R, uint32_t grid_blocks, int dev) {
+  return launch_grid(n, R, grid_blocks, (uint64_t)device_cus(dev) * blocks_per_cu(reg));
 }
 
 // Workgroups for an automatic launch of `grid` (a tile each) over n records:
@@ -1807,9 +1817,10 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
       set_last_error("per-host statistics need fewer than 2^32 records per call");
       return GNM_E_INVAL;
     }
-    if (ht->work_bytes < host_work_bytes(rec->n, grid)) {
+    const uint64_t need = host_work_bytes(rec->n, sized_grid(reg, rec->n, R, p.grid_blocks, dev));
+    if (ht->work_bytes < need) {
       set_last_error("host table: work buffer of " + std::to_string(ht->work_bytes) + " bytes, " +
-                     std::to_string(host_work_bytes(rec->n, grid)) + " needed (gnm_host_work_bytes)");
+                     std::to_string(need) + " needed (gnm_host_work_bytes)");
       return GNM_E_INVAL;
     }
   }
@@ -2205,7 +2216,7 @@ extern "C" int gnm_classify_flag_static(const gnm_registry *reg, const gnm_recor
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
   if (dev != reg->device) { set_last_error("registry belongs to another device"); return GNM_E_INVAL; }
   if (reg->acc_in_lds && rec->n > 0) {
-    const uint64_t grid = launch_grid(reg, rec->n, R, p.grid_blocks, dev);
+    const uint64_t grid = sized_grid(reg, rec->n, R, p.grid_blocks, dev);
     const uint64_t need = partial_bytes(reg, grid);
     if (need > kStaticScratchBytes) {
       set_last_error("the partial tables of " + std::to_string(grid) + " workgroups x " +
