@@ -521,8 +521,9 @@ typedef struct {
 
 /*
  * gnm_autotune — time gnm_classify_aggregate on the caller's own records for
- * candidate launch shapes (records per lane 4, 2, 1 x automatic, half, double
- * and quadruple workgroup counts), each as a warm-up plus the median of `reps`
+ * candidate launch shapes (records per lane 4, 2, 1 x the automatic workgroup
+ * count and half, one, two and four times as many as LDS lets the device hold
+ * at once, each count once), each as a warm-up plus the median of `reps`
  * (0 = 3) timed calls on `stream`, and return the fastest.  acc is
  * overwritten (initialised per call unless base->flags has GNM_ACCUMULATE,
  * in which case it accumulates every timed call).  Without a workspace

@@ -109,15 +109,14 @@ extern "C" int gnm_autotune(const gnm_registry *reg, const gnm_records *rec, con
   *out = gnm_tune_result{};
   const gnm_params b = base ? *base : gnm_params_default();
   if (reps == 0) reps = 3;
-  int dev = -1, cus = 0;
+  int dev = -1;
   hipError_t e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return hip_err(e, "device query");
-  const uint32_t per_cu = reg->lds_bytes <= kLdsMax / 2 ? 2u : 1u;
-  const uint32_t resident = (uint32_t)cus * per_cu;
-  // candidate launch shapes: records per lane x workgroups (0 = automatic)
+  if (e != hipSuccess) return hip_err(e, "hipGetDevice");
+  const uint32_t resident = resident_grid(reg, dev);
+  // candidate launch shapes: records per lane x workgroups (0 = automatic),
+  // without the count that the automatic launch has
   const uint32_t rpts[] = {4, 2, 1};
-  std::vector<uint32_t> grids = {0, resident / 2, resident * 2, resident * 4};
+  const uint32_t grids[] = {0, resident / 2, resident, resident * 2, resident * 4};
   hipEvent_t e0 = nullptr, e1 = nullptr;
   e = hipEventCreate(&e0);
   if (e == hipSuccess) e = hipEventCreate(&e1);
@@ -134,6 +133,7 @@ extern "C" int gnm_autotune(const gnm_registry *reg, const gnm_records *rec, con
       gnm_params p = b;
       p.records_per_thread = rpt;
       p.grid_blocks = grid;
+      if (grid && grid == automatic_grid(reg, rec->n, n_windows, p, dev)) continue;
       // warm-up, then the median of `reps` timed launches
       rc = gnm_classify_aggregate(reg, rec, window_offsets, n_windows, &p, acc, stream);
       if (rc != GNM_OK) break;

@@ -1717,6 +1717,15 @@ uint64_t split_tiles(const gnm_registry *reg, uint64_t n, uint64_t grid, uint32_
 }
 
 }  // namespace
+
+uint64_t automatic_grid(const gnm_registry *reg, uint64_t n, uint32_t n_windows, const gnm_params &p, int dev) {
+  const uint32_t R = p.records_per_thread ? p.records_per_thread : 4u;
+  const uint64_t grid = launch_grid(reg, n, R, 0u, dev);
+  return R == 4u ? split_tiles(reg, n, grid, n_windows, p, dev) : grid;
+}
+
+uint32_t resident_grid(const gnm_registry *reg, int dev) { return (uint32_t)device_cus(dev) * blocks_per_cu(reg); }
+
 }  // namespace gnm
 
 using namespace gnm;
@@ -1790,8 +1799,8 @@ int classify_impl(const gnm_registry *reg, const gnm_records *rec, const uint64_
   if (dev != reg->device) { set_last_error("registry belongs to another device"); return GNM_E_INVAL; }
 
   const uint64_t rows = reg->rows();
-  uint64_t grid = launch_grid(reg, rec->n, R, p.grid_blocks, dev);
-  if (R == 4u && !p.grid_blocks) grid = split_tiles(reg, rec->n, grid, n_windows, p, dev);
+  const uint64_t grid = p.grid_blocks ? launch_grid(reg, rec->n, R, p.grid_blocks, dev)
+                                      : automatic_grid(reg, rec->n, n_windows, p, dev);
   if ((uint64_t)n_windows * rows * 8u > (uint64_t)INT32_MAX * 256u) {
     set_last_error("accumulator tables too large");
     return GNM_E_INVAL;

@@ -45,4 +45,8 @@ namespace gnm {
 void set_last_error(const std::string &s);
 int classify_prepare(const gnm_registry *reg, const gnm_records *rec, const uint64_t *window_offsets,
                      uint32_t n_windows, const gnm_params *p, gnm_acc *acc, uint8_t *flags);
+// Workgroups of an automatic classify launch (p->grid_blocks = 0), and as many
+// as LDS lets a device hold at once.
+uint64_t automatic_grid(const gnm_registry *reg, uint64_t n, uint32_t n_windows, const gnm_params &p, int dev);
+uint32_t resident_grid(const gnm_registry *reg, int dev);
 }

@@ -59,7 +59,9 @@ def _resident(reg: Registry) -> int:
 
 
 def candidate_grids(reg: Registry):
-    """Workgroup counts gnm_autotune tries (the automatic count is the resident one)."""
+    """Workgroup counts gnm_autotune tries beside the automatic launch (which is left out here, and
+    has one of them, a workgroup per CU or a tile each): as many as LDS lets the device hold, half,
+    twice and four times."""
     r = _resident(reg)
     return [r, r // 2, 2 * r, 4 * r]
 
