@@ -1,9 +1,9 @@
 """Autotuning cache for the batched form.
 
 gnm_autotune (C ABI) times launch shapes on the caller's own records; this
-module remembers the winner in a JSON file keyed by device, library version,
-registry shape and workload size, so later runs of the same workload skip the
-search.  The cache holds launch parameters only, never results.
+module remembers the winner in a JSON file keyed by device, library version and
+launch revision, registry shape and workload size, so later runs of the same
+workload skip the search.  The cache holds launch parameters only, never results.
 """
 from __future__ import annotations
 
@@ -13,6 +13,9 @@ import os
 from typing import Dict, Optional
 
 from . import Registry, autotune, lib, version
+
+# Raised when kernels or launch rules change, so that winners timed on the older ones are timed again.
+LAUNCH_REVISION = 2
 
 DEFAULT_CACHE = os.path.join(os.environ.get("XDG_CACHE_HOME", os.path.expanduser("~/.cache")), "gnm", "tune.json")
 
@@ -39,7 +42,7 @@ def workload_key(reg: Registry, n_records: int, n_windows: int, workspace_bytes:
     # the workspace holds (candidates beyond it are not timed)
     g = max_grid_for(reg, workspace_bytes, n_records, n_windows) if workspace_bytes else 0
     merge = "atomic" if not g else ("ws%d" if i["acc_in_lds"] else "spill%d") % g
-    return "%s|%s|%s|n2^%d|w2^%d|%s" % (_device_name(), version(), shape, nb, wb, merge)
+    return "%s|%s/%d|%s|n2^%d|w2^%d|%s" % (_device_name(), version(), LAUNCH_REVISION, shape, nb, wb, merge)
 
 
 def max_grid_for(reg: Registry, workspace_bytes: int, n_records: int = 0, n_windows: int = 1) -> int:
