@@ -9,7 +9,7 @@
 //      the record counts (0 = rejected) within blocks of 1,024 datagrams;
 //   2. v5_decode_kernel: one workgroup per 32 datagrams.  It sums the block
 //      totals before its own (a one-workgroup v5_scan_kernel does that first
-//      for more than 4,096 blocks), reads its records as contiguous 16-byte
+//      for more than 2,048 blocks), reads its records as contiguous 16-byte
 //      pieces into LDS, and writes each output field with full-wave
 //      coalesced stores, lane i decoding record i of the tile.
 // Up to 2,048 datagrams need no first kernel: every decode workgroup counts
@@ -51,7 +51,12 @@ constexpr uint32_t kPieces = 3;            // 16-byte pieces of a record
 constexpr uint32_t kPieceLoads = 6;        // pieces in flight per lane
 constexpr uint32_t kSmallPer = 8;          // single-launch form: datagrams per lane
 constexpr uint64_t kSmall = (uint64_t)kThreads * kSmallPer;
-constexpr uint32_t kInlineBlocks = 4096;   // block totals a decode workgroup sums itself
+// Block totals a decode workgroup sums itself, which saves the scan kernel's
+// launch (10,000 datagrams of 30 records 13.3 us a call, 15.9 with it) until it
+// reads too many: 1 M datagrams (977 blocks) 484 and 490 us, 2 M 982 and 986,
+// 4.2 M (4,096 blocks) 2,270 and 2,095.  (Between 100 and 350 blocks the two are
+// within 1.5 us, the scan kernel ahead.)
+constexpr uint32_t kInlineBlocks = 2048;
 constexpr uint32_t kScanThreads = 1024;
 constexpr uint32_t kCountBits = 5;         // a scanned count: records before it in its block << 5 | records
 static_assert(kV5MaxRecords < (1u << kCountBits) && kBlock % kTile == 0 && kSmall % kTile == 0, "packed counts");
@@ -281,7 +286,7 @@ __global__ __launch_bounds__(kThreads) void v5_decode_kernel(const DecodeArgs q)
       for (uint64_t i = tid; i < upto; i += kThreads) {
         const u64 v = q.sums[i];
         sum += i < b ? v & 0xFFFFFFFFull : 0ull;
-        all += v;  // workgroup 0: at most 4,096 blocks, so both halves fit
+        all += v;  // workgroup 0: at most 2,048 blocks, so both halves fit
       }
       sum = wave_sum(sum);
       if (tid % 64u == 0u) wsum[tid / 64u] = sum;
