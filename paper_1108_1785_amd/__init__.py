@@ -160,6 +160,7 @@ class GnmError(RuntimeError):
 
 
 _lib = None
+_defaults = b""  # gnm_params_default() of the loaded library, asked for once
 
 
 def _lib_or_none():
@@ -168,7 +169,7 @@ def _lib_or_none():
 
 def lib():
     """The loaded libgnm.so; raises if it has not been built."""
-    global _lib
+    global _lib, _defaults
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError("libgnm.so is not built (run python -m paper_1108_1785_amd._build); "
@@ -231,6 +232,7 @@ def lib():
         L.gnm_last_error.restype = ctypes.c_char_p
         L.gnm_version.argtypes = []
         L.gnm_version.restype = ctypes.c_char_p
+        _defaults = bytes(L.gnm_params_default())
         _lib = L
     return _lib
 
@@ -364,8 +366,11 @@ def make_params(bulk_bytes: int = 1_000_000, accumulate: bool = False, records_p
     hosts: optional HostTable (the caller keeps it alive while work is queued).
     flush_records: records a workgroup aggregates between table flushes (0 = 2^31)."""
     lib()  # raises when it has not been built
-    # (gnm_params_default's one non-zero field is bulk_bytes, given here)
-    p = Params(int(bulk_bytes), GNM_ACCUMULATE if accumulate else 0, int(records_per_thread), int(grid_blocks))
+    p = Params.from_buffer_copy(_defaults)
+    p.bulk_bytes = int(bulk_bytes)
+    p.flags = GNM_ACCUMULATE if accumulate else 0
+    p.records_per_thread = int(records_per_thread)
+    p.grid_blocks = int(grid_blocks)
     if not 0 <= int(flush_records) < 2**32:
         raise ValueError("flush_records must fit 32 bits")
     p.flush_records = int(flush_records)
@@ -378,6 +383,7 @@ def make_params(bulk_bytes: int = 1_000_000, accumulate: bool = False, records_p
         if not rate_hist.is_cuda or not rate_hist.is_contiguous() or rate_hist.element_size() != 4:
             raise ValueError("rate_hist must be a contiguous device tensor of 32-bit counts")
         p.rate_hist = rate_hist.data_ptr()
+    p.min_avg_packet_bytes = p.min_packets = p.min_duration_ms = 0
     if filters:
         f = dict(filters)
         if set(f) - set(FILTER_KEYS):
