@@ -1,5 +1,5 @@
-// Partitioning of staged entries, shared by the per-host statistics
-// (hosts.hip) and the spilled accumulator tables (table.hip).
+// Partitioning of staged entries, shared by the rate histograms (hist.hip) and
+// the per-host statistics (hosts.hip).
 //
 // A classify workgroup b stages entries in its own range [lo_b, lo_b +
 // count[b]) of an entry array, [lo_b, hi_b) being its slice of the records.
@@ -16,9 +16,8 @@
 // threads once the totals tot[0..64) of partitions p0 .. p0 + 63 are in LDS,
 // and every scatter workgroup b of `grid` calls `Traits::scatter_share(tot,
 // P, t, b, grid)` with all the totals in LDS.
-// Entries of 16-byte multiples are copied as 16-byte words, smaller ones
-// whole.  The count kernel can be left out when the producer writes the
-// count matrix itself.
+// Entries are one 16-byte word, or smaller.  The count kernel can be left out
+// when the producer writes the count matrix itself.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -39,7 +38,6 @@ struct PartArgs {
   const E *stage;
   const uint32_t *scount;  // [grid]
   uint64_t n;              // records of the classify launch
-  uint64_t extra;          // entries each workgroup's range holds beyond its records
   uint32_t grid, nparts;   // classify workgroups; partitions (a multiple of 64)
   uint32_t *phist;         // [grid][nparts]: counts, then each workgroup's offset within the partition
   uint32_t *ptotal, *pbase;  // [nparts]
@@ -48,12 +46,6 @@ struct PartArgs {
   u64 *clear;              // words set to 0 by the count kernel before anything else reads them
   uint32_t nclear;
 };
-
-// First staged entry of classify workgroup b: its first record, plus the
-// extra room of the workgroups before it.
-__device__ __forceinline__ uint64_t part_stage_lo(uint32_t b, uint64_t n, uint32_t grid, uint64_t extra) {
-  return slice_lo(b, n, grid) + (uint64_t)b * extra;
-}
 
 // Partition counts of classify workgroup b's entries (dynamic LDS: nparts
 // counters).  Workgroup 0 also clears the caller's counter words.
@@ -64,7 +56,7 @@ __global__ __launch_bounds__(kPartThreads) void part_count_kernel(const PartArgs
   for (uint32_t p = threadIdx.x; p < P; p += kPartThreads) h[p] = 0u;
   if (b == 0 && threadIdx.x < q.nclear) q.clear[threadIdx.x] = 0;
   __syncthreads();
-  const uint64_t lo = part_stage_lo(b, q.n, q.grid, q.extra);
+  const uint64_t lo = slice_lo(b, q.n, q.grid);  // a range starts at its slice's first record
   const uint32_t cnt = q.scount[b];
   // kPartUnroll entries per lane loaded before their counts are added
   for (uint32_t i0 = 0; i0 < cnt; i0 += kPartUnroll * kPartThreads) {
@@ -191,56 +183,26 @@ __global__ __launch_bounds__(kPartThreads) void part_scatter_kernel(const PartAr
   const uint32_t *off = q.phist + (uint64_t)b * P;
   for (uint32_t p = threadIdx.x; p < P; p += kPartThreads) cur[p] += off[p];
   __syncthreads();
-  const uint64_t lo = part_stage_lo(b, q.n, q.grid, q.extra);
+  const uint64_t lo = slice_lo(b, q.n, q.grid);  // a range starts at its slice's first record
   const uint32_t cnt = q.scount[b];
-  if constexpr (sizeof(E) % 16 != 0) {
-    // small entries: kPartUnroll per lane in flight, copied whole
-    for (uint32_t i0 = 0; i0 < cnt; i0 += kPartUnroll * kPartThreads) {
-      E v[kPartUnroll];
-      uint32_t pos[kPartUnroll];
-#pragma unroll
-      for (uint32_t j = 0; j < kPartUnroll; ++j) {
-        const uint32_t i = i0 + j * kPartThreads + threadIdx.x;
-        if (i < cnt) v[j] = q.stage[lo + i];
-      }
-#pragma unroll
-      for (uint32_t j = 0; j < kPartUnroll; ++j) {
-        const uint32_t i = i0 + j * kPartThreads + threadIdx.x;
-        pos[j] = i < cnt ? atomicAdd(&cur[T::part(v[j], t)], 1u) : 0u;
-      }
-#pragma unroll
-      for (uint32_t j = 0; j < kPartUnroll; ++j)
-        if (i0 + j * kPartThreads + threadIdx.x < cnt) q.part[pos[j]] = v[j];
-    }
-    return;
-  }
+  static_assert(sizeof(E) <= 16, "an entry is at most one 16-byte word");
   // kPartUnroll entries per lane in flight: loaded, then placed, then stored
-  typedef u64 u64x2p __attribute__((ext_vector_type(2)));
-  constexpr uint32_t W = sizeof(E) / 16 ? sizeof(E) / 16 : 1u;
   for (uint32_t i0 = 0; i0 < cnt; i0 += kPartUnroll * kPartThreads) {
-    u64x2p v[kPartUnroll][W];
+    E v[kPartUnroll];
     uint32_t pos[kPartUnroll];
 #pragma unroll
     for (uint32_t j = 0; j < kPartUnroll; ++j) {
       const uint32_t i = i0 + j * kPartThreads + threadIdx.x;
-      if (i < cnt) {
-#pragma unroll
-        for (uint32_t k = 0; k < W; ++k) v[j][k] = ((const u64x2p *)(q.stage + lo + i))[k];
-      }
+      if (i < cnt) v[j] = q.stage[lo + i];
     }
 #pragma unroll
     for (uint32_t j = 0; j < kPartUnroll; ++j) {
       const uint32_t i = i0 + j * kPartThreads + threadIdx.x;
-      pos[j] = i < cnt ? atomicAdd(&cur[T::part(*(const E *)v[j], t)], 1u) : 0u;
+      pos[j] = i < cnt ? atomicAdd(&cur[T::part(v[j], t)], 1u) : 0u;
     }
 #pragma unroll
-    for (uint32_t j = 0; j < kPartUnroll; ++j) {
-      const uint32_t i = i0 + j * kPartThreads + threadIdx.x;
-      if (i < cnt) {
-#pragma unroll
-        for (uint32_t k = 0; k < W; ++k) ((u64x2p *)(q.part + pos[j]))[k] = v[j][k];
-      }
-    }
+    for (uint32_t j = 0; j < kPartUnroll; ++j)
+      if (i0 + j * kPartThreads + threadIdx.x < cnt) q.part[pos[j]] = v[j];
   }
 }
 
