@@ -103,6 +103,13 @@ __device__ __forceinline__ uint32_t split_of(const Merge &q, uint32_t hot, uint3
   return hot / (least > fit ? least : fit);
 }
 
+// What the merge looks up of a classify workgroup: its slice, the entries that a
+// part of its range holds, and those that the tile's has.
+struct Looked {
+  uint64_t lo, hi;
+  uint32_t cap, in;
+};
+
 // Sum of `hot` over the tiles (every lane takes part; s: a word per wave).
 __device__ __forceinline__ uint32_t sum_hot(const Merge &q, uint32_t *s) {
   uint32_t x = 0;
@@ -130,6 +137,23 @@ __device__ __forceinline__ uint64_t part_lo(const Merge &q, uint32_t b) {
   return b < q.grid ? scaled(b, q.n, q.grid) & ~3ull : q.n;
 }
 
+// Mean-rate test of the registered sites whose rows lie among the nr from r0 on
+// of window w; `rows`: those rows, `stride` words apart.
+__device__ __forceinline__ void flag_rows(const Merge &q, uint32_t w, uint32_t r0, uint32_t nr, const u64 *rows,
+                                          uint32_t stride) {
+  for (uint32_t j = threadIdx.x; 2u * j < nr; j += kTableThreads) {
+    const uint32_t site = r0 / 2u + j;
+    if (site >= q.fl.n_sites) continue;
+    uint8_t fv = 0;
+#pragma unroll
+    for (uint32_t d = 0; d < 2u; ++d) {
+      const u64 nb = rows[(2u * j + d) * stride + 4u], sum = rows[(2u * j + d) * stride + 5u];
+      if (nb >= q.fl.need && sum / nb < q.fl.threshold) fv |= (uint8_t)(1u << d);
+    }
+    q.fl.flags[(uint64_t)w * q.fl.n_sites + site] = fv;
+  }
+}
+
 // Workgroups 0 .. n_windows * tiles - 1: one per (window, tile), the first of
 // those that share the tile.  Beyond: q.more per window, the e-th of a window
 // taking the e-th share of its shared tiles, if there are that many.  LDS rows
@@ -137,7 +161,8 @@ __device__ __forceinline__ uint64_t part_lo(const Merge &q, uint32_t b) {
 // min, max (the device-table order).
 __global__ __launch_bounds__(kTableThreads, 8) void table_reduce_kernel(const Merge q) {
   extern __shared__ __align__(16) u64 t[];
-  __shared__ uint32_t s_sum[kTableThreads / 64], s_all[kTableThreads / 64], s_tile, s_share;
+  __shared__ uint32_t s_sum[kTableThreads / 64], s_all[kTableThreads / 64], s_tile, s_share, s_b[2];
+  __shared__ Looked s_look[64];
   const uint32_t lane = threadIdx.x % 64u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);
   uint32_t w, tile, share = 0;
   if (blockIdx.x < q.n_windows * q.tiles) {
@@ -187,12 +212,7 @@ __global__ __launch_bounds__(kTableThreads, 8) void table_reduce_kernel(const Me
   const uint32_t tile_rows = 1u << q.tile_bits, r0 = tile << q.tile_bits;
   const uint32_t kind_shift = kEntRowShift + q.tile_bits, window_shift = kind_shift + kEntKindBits;
   const uint32_t nr = q.rows - r0 < tile_rows ? q.rows - r0 : tile_rows;
-  for (uint32_t r = threadIdx.x; r < tile_rows; r += kTableThreads) {
-#pragma unroll
-    for (uint32_t f = 0; f < 8u; ++f) t[r * kRowWords + f] = f == 6u ? ~0ull : 0ull;
-  }
-  __syncthreads();
-  const uint32_t shares = hot ? 1u + split_of(q, hot, sum_hot(q, s_all)) : 1u;
+  u64 *acc = q.acc + ((uint64_t)w * q.rows + r0) * 8u;
   // the window's records, as the classify kernel cuts them: the first window
   // starts at record 0, the last ends at record n
   uint64_t wlo = 0, whi = q.n;
@@ -200,6 +220,57 @@ __global__ __launch_bounds__(kTableThreads, 8) void table_reduce_kernel(const Me
     if (w > 0) wlo = q.woff[w] < q.n ? q.woff[w] : q.n;
     if (w + 1u < q.n_windows) whi = q.woff[w + 1u] < q.n ? q.woff[w + 1u] : q.n;
   }
+  // The nb classify workgroups from bfirst on whose slices may meet it, looked
+  // up 64 at a time, a lane for each: slice and entries of the part.  Of up to 64
+  // the first wave looks them up for all (16 waves' divisions would bound a call
+  // of many small windows); a tile without entries, as most are in a small
+  // window, then has nothing to add, only its flags to test.
+  uint32_t bfirst = 0, nb = 0, in_l = 0, cap_l = 0;
+  uint64_t lo_l = 0, hi_l = 0;
+  auto look_up = [&](uint32_t k0, uint32_t step) {
+    const uint32_t kl = k0 + lane * step, bl = bfirst + (kl < nb ? kl : 0u);
+    lo_l = part_lo(q, bl);
+    hi_l = part_lo(q, bl + 1u);
+    cap_l = table_range(hi_l - lo_l, q.extra, q.tiles).cap;
+    const bool meets = kl < nb && lo_l < whi && hi_l > wlo && lo_l < hi_l;
+    in_l = meets ? q.count[(uint64_t)bl * q.tiles + tile] : 0u;
+  };
+  if (wave == 0u) {
+    if (wlo < whi) {
+      bfirst = (uint32_t)scaled(wlo, q.grid, q.n);
+      bfirst = bfirst ? bfirst - 1u : 0u;
+      const uint32_t blast = (uint32_t)scaled(whi - 1u, q.grid, q.n) + 1u;
+      nb = (blast < q.grid ? blast : q.grid - 1u) - bfirst + 1u;
+    }
+    if (nb <= 64u) {
+      look_up(0u, 1u);
+      s_look[lane] = Looked{lo_l, hi_l, cap_l, in_l};
+    }
+    if (lane == 0u) {
+      s_b[0] = bfirst;
+      s_b[1] = nb;
+    }
+  }
+  for (uint32_t r = threadIdx.x; r < tile_rows; r += kTableThreads) {
+#pragma unroll
+    for (uint32_t f = 0; f < 8u; ++f) t[r * kRowWords + f] = f == 6u ? ~0ull : 0ull;
+  }
+  __syncthreads();
+  bfirst = __builtin_amdgcn_readfirstlane(s_b[0]);
+  nb = __builtin_amdgcn_readfirstlane(s_b[1]);
+  const bool few = nb <= 64u;
+  if (few) {
+    const Looked x = s_look[lane];
+    lo_l = x.lo;
+    hi_l = x.hi;
+    cap_l = x.cap;
+    in_l = x.in;
+    if (__builtin_amdgcn_ballot_w64(in_l != 0u) == 0ull) {
+      if (share == 0u && q.fl.flags) flag_rows(q, w, r0, nr, acc, 8u);
+      return;
+    }
+  }
+  const uint32_t shares = hot ? 1u + split_of(q, hot, sum_hot(q, s_all)) : 1u;
   // one entry into its row
   auto add = [&](u64 v, u64 y) {
     u64 *o = t + ((uint32_t)(y >> kEntRowShift) & (tile_rows - 1u)) * kRowWords;
@@ -230,78 +301,75 @@ __global__ __launch_bounds__(kTableThreads, 8) void table_reduce_kernel(const Me
       atomicAdd(&o[kind == kRowRateSum ? 5u : kind - kRowBytes + 1u], v);
     }
   };
-  // classify workgroups whose slices meet it, a wave of the tile's workgroups
-  // for each, or several where there are fewer of them than waves; four entries
-  // per lane in flight
+  // A wave of the tile's workgroups for each of the nb, or several where there
+  // are fewer of them than waves; four entries per lane in flight.
   constexpr uint32_t U = 4;
-  if (wlo < whi) {
-    uint32_t bfirst = (uint32_t)scaled(wlo, q.grid, q.n), blast = (uint32_t)scaled(whi - 1u, q.grid, q.n) + 1u;
-    bfirst = bfirst ? bfirst - 1u : 0u;
-    blast = blast < q.grid ? blast : q.grid - 1u;
-    const uint32_t nb = blast - bfirst + 1u, waves = shares * (kTableThreads / 64u);
-    const uint32_t me = share * (kTableThreads / 64u) + wave, subs = waves > nb ? waves / nb : 1u;
-    const uint32_t sub = waves > nb ? me / nb : 0u, step = waves > nb ? nb : waves;
-    for (uint32_t k0 = me - sub * nb; sub < subs && k0 < nb; k0 += 64u * step) {
-      // up to 64 of the wave's workgroups, a lane for each: its slice and its
-      // part's entries
-      const uint32_t kl = k0 + lane * step, bl = bfirst + (kl < nb ? kl : 0u);
-      const uint64_t lo_l = part_lo(q, bl), hi_l = part_lo(q, bl + 1u);
-      const uint32_t cap_l = table_range(hi_l - lo_l, q.extra, q.tiles).cap;
-      const bool meets = kl < nb && lo_l < whi && hi_l > wlo && lo_l < hi_l;
-      const uint32_t in_l = meets ? q.count[(uint64_t)bl * q.tiles + tile] : 0u;
-      for (uint64_t todo = __builtin_amdgcn_ballot_w64(in_l != 0u); todo; todo &= todo - 1u) {
-        const uint32_t l = (uint32_t)__builtin_ctzll(todo);
-        const uint32_t in = (uint32_t)__builtin_amdgcn_readlane((int)in_l, l), b = bfirst + k0 + l * step;
-        const uint64_t lo = readlane64(lo_l, l), hi = readlane64(hi_l, l);
-        const char *range = q.entry + kTableRangeBytes * (lo + (uint64_t)b * q.extra);
-        const TableEntry *e = (const TableEntry *)range + (uint64_t)tile * (uint32_t)__builtin_amdgcn_readlane((int)cap_l, l);
-        uint32_t i0 = 0, end = in & ~kTableMore;
+  const uint32_t waves = shares * (kTableThreads / 64u), me = share * (kTableThreads / 64u) + wave;
+  const uint32_t subs = waves > nb ? waves / nb : 1u, sub = waves > nb ? me / nb : 0u;
+  const uint32_t mine0 = sub < subs ? me - sub * nb : nb;  // the wave's first (nb: a wave too many)
+  const uint32_t step = few ? 1u : (waves < nb ? waves : nb);
+  uint64_t own = ~0ull;
+  if (few) {
+    own = 0ull;
+    for (uint32_t l = mine0; l < nb; l += waves) own |= 1ull << l;
+  }
+  for (uint32_t k0 = few ? 0u : mine0; k0 < nb; k0 += 64u * step) {
+    if (!few) look_up(k0, step);
+    for (uint64_t todo = __builtin_amdgcn_ballot_w64(in_l != 0u) & own; todo; todo &= todo - 1u) {
+      const uint32_t l = (uint32_t)__builtin_ctzll(todo);
+      const uint32_t in = (uint32_t)__builtin_amdgcn_readlane((int)in_l, l), b = bfirst + k0 + l * step;
+      const uint64_t lo = readlane64(lo_l, l), hi = readlane64(hi_l, l);
+      const char *range = q.entry + kTableRangeBytes * (lo + (uint64_t)b * q.extra);
+      const TableEntry *e = (const TableEntry *)range + (uint64_t)tile * (uint32_t)__builtin_amdgcn_readlane((int)cap_l, l);
+      // the window's entries (of a short part, all: they are tested below, and a
+      // search takes a round trip for every halving)
+      uint32_t i0 = 0, end = in & ~kTableMore;
+      if (end > U * 64u) {
         if (lo < wlo) i0 = first_of_window(e, end, w, window_shift);
         if (hi > whi) end = i0 + first_of_window(e + i0, end - i0, w + 1u, window_shift);
-        // then the tile's chunks, as places after the part's: place i of them
-        // all is place i mod chunk of chunk i / chunk
-        const uint32_t in_part = end - i0;
-        e += i0;
-        uint32_t places = in_part, bits = 0;
-        const TableChunk *list = nullptr;
-        const TableEntry *ce = nullptr;
-        if (in & kTableMore) {
-          const TableRange rg = table_range(hi - lo, q.extra, q.tiles);
-          const uint32_t *first = (const uint32_t *)(range + rg.first) + tile;
-          list = (const TableChunk *)(range + rg.list()) + first[0];
-          ce = (const TableEntry *)(range + rg.entries());
-          bits = rg.bits;
-          places += (first[1] - first[0]) << bits;
-        }
-        for (i0 = sub * U * 64u; i0 < places; i0 += subs * U * 64u) {
-          u64x2 x[U];
-          uint32_t mine = 0;
+      }
+      // then the tile's chunks, as places after the part's: place i of them
+      // all is place i mod chunk of chunk i / chunk
+      const uint32_t in_part = end - i0;
+      e += i0;
+      uint32_t places = in_part, bits = 0;
+      const TableChunk *list = nullptr;
+      const TableEntry *ce = nullptr;
+      if (in & kTableMore) {
+        const TableRange rg = table_range(hi - lo, q.extra, q.tiles);
+        const uint32_t *first = (const uint32_t *)(range + rg.first) + tile;
+        list = (const TableChunk *)(range + rg.list()) + first[0];
+        ce = (const TableEntry *)(range + rg.entries());
+        bits = rg.bits;
+        places += (first[1] - first[0]) << bits;
+      }
+      for (i0 = sub * U * 64u; i0 < places; i0 += subs * U * 64u) {
+        u64x2 x[U];
+        uint32_t mine = 0;
 #pragma unroll
-          for (uint32_t j = 0; j < U; ++j) {
-            uint32_t i = i0 + j * 64u + lane;
-            const TableEntry *at = e + i;
-            bool ok = i < in_part;
-            if (!ok && i < places) {
-              i -= in_part;
-              const u32x4 c = *(const u32x4 *)(list + (i >> bits));  // id, first, count, last
-              i &= (1u << bits) - 1u;
-              at = ce + ((uint64_t)c.x << bits) + i;
-              ok = i < c.z && c.y <= w && w <= c.w;
-            }
-            if (ok) x[j] = *(const u64x2 *)at;
-            mine |= (uint32_t)ok << j;
+        for (uint32_t j = 0; j < U; ++j) {
+          uint32_t i = i0 + j * 64u + lane;
+          const TableEntry *at = e + i;
+          bool ok = i < in_part;
+          if (!ok && i < places) {
+            i -= in_part;
+            const u32x4 c = *(const u32x4 *)(list + (i >> bits));  // id, first, count, last
+            i &= (1u << bits) - 1u;
+            at = ce + ((uint64_t)c.x << bits) + i;
+            ok = i < c.z && c.y <= w && w <= c.w;
           }
-#pragma unroll
-          for (uint32_t j = 0; j < U; ++j)
-            if (((mine >> j) & 1u) && (uint32_t)(x[j].y >> window_shift) == w) add(x[j].x, x[j].y);
+          if (ok) x[j] = *(const u64x2 *)at;
+          mine |= (uint32_t)ok << j;
         }
+#pragma unroll
+        for (uint32_t j = 0; j < U; ++j)
+          if (((mine >> j) & 1u) && (uint32_t)(x[j].y >> window_shift) == w) add(x[j].x, x[j].y);
       }
     }
   }
   __syncthreads();
   // the rows of the device table: word f of row r of window w, one word per
   // lane, consecutive lanes on consecutive words
-  u64 *acc = q.acc + ((uint64_t)w * q.rows + r0) * 8u;
   if (shares == 1u) {
     for (uint32_t i = threadIdx.x; i < nr * 8u; i += kTableThreads) {
       const uint32_t r = i / 8u, f = i % 8u;
@@ -339,17 +407,7 @@ __global__ __launch_bounds__(kTableThreads, 8) void table_reduce_kernel(const Me
     }
     __syncthreads();
   }
-  // mean-rate test of the registered sites whose rows lie in this range
-  for (uint32_t j = threadIdx.x; 2u * j < nr; j += kTableThreads) {
-    const uint32_t site = r0 / 2u + j;
-    if (site >= q.fl.n_sites) continue;
-    uint8_t fv = 0;
-    for (uint32_t d = 0; d < 2u; ++d) {
-      const u64 nb = t[(2u * j + d) * kRowWords + 4u], sum = t[(2u * j + d) * kRowWords + 5u];
-      if (nb >= q.fl.need && sum / nb < q.fl.threshold) fv |= (uint8_t)(1u << d);
-    }
-    q.fl.flags[(uint64_t)w * q.fl.n_sites + site] = fv;
-  }
+  flag_rows(q, w, r0, nr, t, kRowWords);
 }
 
 }  // namespace
@@ -382,7 +440,7 @@ TableStage table_stage(void *work, uint64_t n, uint64_t grid, uint32_t n_windows
   t.count = (uint32_t *)(wb + kTableRangeBytes * (n + grid * table_extra(slots)));
   t.hot = t.count + grid * tiles;
   t.done = t.hot + tiles;
-  t.more = table_more(n, n_windows);
+  t.more = table_more(n, n_windows, tiles);
   t.words = t.more ? tiles + n_windows * tiles : 0u;
   return t;
 }
