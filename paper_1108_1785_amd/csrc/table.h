@@ -64,14 +64,12 @@ constexpr uint64_t kTableRangeBytes = 64;
 inline uint64_t table_extra(uint32_t slots) { return 6ull * slots; }
 
 // Merge workgroups per window beyond one per tile, to share tiles of many
-// entries: at most 256 over all windows.  None for short runs, where clearing
-// their counters costs more (20,000 records on 20,000 sites 24.5 us a call
-// without, 27 with them), from fewer records on where tiles are many and wide
-// (100,000 records on 1,000 of 1,000,000 sites 252 us without, 100 with them).
-inline uint32_t table_more(uint64_t n, uint32_t n_windows, uint32_t tiles) {
+// entries: at most 256 over all windows, and none for the shortest runs (100,000
+// records on 1,000 of 1,000,000 sites 252 us a call without, 100 with them; Zipf
+// on 20,000 sites, with host statistics, 102 and 77).
+inline uint32_t table_more(uint64_t n, uint32_t n_windows) {
   const uint64_t useful = n >> 11;
-  if (n < (tiles <= kTilesTarget / 2u ? 1u << 17 : 1u << 15)) return 0u;
-  return (uint32_t)(useful < 256u ? useful : 256u) / n_windows;
+  return n < (1u << 15) ? 0u : (uint32_t)(useful < 256u ? useful : 256u) / n_windows;
 }
 
 // Tiles of a table, and the bits of a tile's rows.

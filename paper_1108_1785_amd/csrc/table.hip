@@ -440,7 +440,7 @@ TableStage table_stage(void *work, uint64_t n, uint64_t grid, uint32_t n_windows
   t.count = (uint32_t *)(wb + kTableRangeBytes * (n + grid * table_extra(slots)));
   t.hot = t.count + grid * tiles;
   t.done = t.hot + tiles;
-  t.more = table_more(n, n_windows, tiles);
+  t.more = table_more(n, n_windows);
   t.words = t.more ? tiles + n_windows * tiles : 0u;
   return t;
 }
