@@ -352,17 +352,31 @@ __device__ __forceinline__ void reduce_lists(ListMap &m, Shared &sh, const Parts
   __syncthreads();
   const uint32_t queued = sh.queued[g];
   for (uint32_t j = wv; j < queued; j += kHostThreads / 64u) {
-    // the smallest bucket with at least `want` flows at or below it
+    // the smallest bucket with at least `want` flows at or below it, a quarter
+    // of the range left by each of 7 passes over the list, 8 words of a lane in
+    // flight (14 halvings, a word at a time: 20 us more for a list of 700)
     const uint32_t sl = m.queue[j], c = m.flows[sl], base = m.base[sl], want = (c + 1u) / 2u;
-    uint32_t lo = 0, hi = (1u << 14) - 1u;
-    while (lo < hi) {
-      const uint32_t mid = (lo + hi) / 2u;
-      uint32_t cnt = 0;
-      for (uint32_t k = lane; k - lane < c; k += 64u)
-        cnt += (uint32_t)__popcll(
-            __ballot(k < c && (m.list[base + (k < c ? k : 0u)] >> (kListSlotBits + kListPlaceBits)) <= mid));
-      if (cnt >= want) hi = mid;
-      else lo = mid + 1u;
+    uint32_t lo = 0;
+    for (uint32_t q4 = (1u << 14) / 4u; q4; q4 /= 4u) {
+      uint32_t below[3] = {0u, 0u, 0u};  // flows below lo + q4, lo + 2 q4, lo + 3 q4
+      for (uint32_t k0 = 0; k0 < c; k0 += 8u * 64u) {
+        uint32_t v[8];
+#pragma unroll
+        for (uint32_t i = 0; i < 8u; ++i) {
+          const uint32_t k = k0 + i * 64u + lane;
+          v[i] = m.list[base + (k < c ? k : 0u)] >> (kListSlotBits + kListPlaceBits) | (k < c ? 0u : 1u << 14);
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < 8u; ++i)
+#pragma unroll
+          for (uint32_t h = 0; h < 3u; ++h) below[h] += (uint32_t)__popcll(__ballot(v[i] < lo + (h + 1u) * q4));
+      }
+#pragma unroll
+      for (uint32_t h = 3; h > 0u; --h)
+        if (below[h - 1u] < want) {
+          lo += h * q4;
+          break;
+        }
     }
     if (lane == 0) m.median[sl] = (uint16_t)lo;
   }
