@@ -501,7 +501,7 @@ def main():
         "alg_bytes_per_call": v5_alg, "decode_gb_s": v5_alg / (ik * 1e-3) / 1e9,
         "reference_copy_gb_s": copy_gbs,
         "ingest_classify_step_ms": float(np.mean(icms)), "ingest_classify_records_per_s": args.steps * n_v5 / wall_ic,
-        "launch": "gnm_netflow_v5_decode (count, 3 scan passes, decode), then classify call + flag"}
+        "launch": "gnm_netflow_v5_decode (count, decode), then classify call + flag"}
     log("ingest: decode %.4f ms (%.1f G records/s, %.0f GB/s; a 1 GiB device copy runs at %.0f GB/s); "
         "decode + classify step %.4f ms" % (ik, n_v5 / (ik * 1e-3) / 1e9, v5_alg / (ik * 1e-3) / 1e9, copy_gbs,
                                             float(np.mean(icms))))

@@ -289,13 +289,16 @@ uint64_t gnm_workspace_bytes(const gnm_registry *reg, uint32_t grid_blocks);
  * For one whose table does not (gnm_registry_info.acc_in_lds == 0), the
  * workspace holds the spilled rows instead: the rows that miss a workgroup's
  * LDS row cache and the cached rows flushed at window changes are staged as
- * 16-byte entries, by ranges of 256 table rows, and merged by one workgroup
- * per (window, 256 table rows), which writes its rows of the table and their
- * flag bytes without device-scope atomics: about 128 bytes per record, so
- * that ranges of unequal use have room.  Without that workspace
- * the rows go to the table with device-scope atomics, with the same results.
- * 0 for a NULL registry, n_windows = 0, or more than 16,384 (window, 256-row)
- * ranges (such calls always use the atomics).
+ * 16-byte entries by tiles of 256 table rows (up to 2,048 in tables of more
+ * than 262,144 rows), and a merge adds each (window, tile) into the table and
+ * writes its flag bytes, with one workgroup per (window, tile) and, in calls of
+ * 32,768 records or more, up to 256 others that share tiles of many entries.
+ * It is 64 bytes per record and 384 per cache row of each workgroup, four
+ * entries for each that can come, so that tiles of unequal use have room, and
+ * a few bytes per workgroup and tile.  Without that workspace the rows go to
+ * the table with device-scope atomics, with the same results.  0 for a NULL
+ * registry, n_windows = 0, or more than 16,384 pairs of a window and 256 rows
+ * (such calls always use the atomics).
  */
 uint64_t gnm_workspace_bytes_n(const gnm_registry *reg, uint64_t n_records, uint32_t n_windows,
                                uint32_t grid_blocks);
@@ -313,7 +316,9 @@ uint64_t gnm_workspace_bytes_n(const gnm_registry *reg, uint64_t n_records, uint
  * workgroup) and one workgroup per range (or per slice of 16,384 keys of a
  * range) counts them in LDS and writes the range's rows of rate_hist whole,
  * so no zeroing pass and no device-scope atomics are needed except for the
- * rows of ranges holding several slices.  Results are the same bit for bit.
+ * rows of ranges holding several slices.  Calls of at most 102,400 records
+ * that have few histogram rows for them need no ordering: one kernel counts
+ * the keys of a row per workgroup.  Results are the same bit for bit.
  * Calls whose n_windows * 2 * n_sites rows pass 65,536, calls of 2^32 records
  * or more, and calls whose workspace is smaller keep the LDS cache and
  * device-scope atomics; for the first two this returns the tables' part
@@ -358,14 +363,15 @@ uint64_t gnm_host_work_bytes(const gnm_registry *reg, uint64_t n_records, uint32
  * With p->rate_hist, each bulk flow of a registered site also adds one to
  * its row's histogram: through an LDS cache and device-scope 32-bit atomics,
  * or, with a workspace of gnm_workspace_bytes_hist, as a staged key, which
- * four more kernels order by row and count (see gnm_workspace_bytes_hist);
- * the caller owns the histogram memory (n_windows * 2 * n_sites *
+ * a scan, a scatter and a counting kernel order by row and count, one kernel
+ * in small calls (see gnm_workspace_bytes_hist); the caller owns the histogram memory (n_windows * 2 * n_sites *
  * GNM_RATE_BUCKETS * 4 bytes).
  * With p->hosts, the classify kernel also stages each such flow (host key,
- * bytes, rate) in p->hosts->work, and four kernels follow: partition counts
- * by a hash of the key, their scan, the scatter into partition order, and one
- * workgroup per partition that gathers the hosts' statistics and medians in
- * LDS and writes them to the table.  Each classify workgroup walks a balanced contiguous slice of all
+ * bytes, duration) in p->hosts->work, and three kernels follow: the scan of
+ * the entries per partition (by a hash of the key; counted by the classify
+ * kernel, or by a kernel of its own where that has no LDS for it), the scatter
+ * into partition order, and one that gathers each partition's host statistics
+ * and medians in LDS and writes them to the table.  Each classify workgroup walks a balanced contiguous slice of all
  * records, flushing its LDS table at window changes.  Errors: GNM_E_INVAL
  * (null pointers, n_windows = 0, offsets NULL with n_windows > 1,
  * records_per_thread not 0/1/2/4, n_windows tables beyond 2^39 words,
@@ -585,8 +591,9 @@ uint64_t gnm_netflow_v5_workspace_bytes(uint64_t n_datagrams);
  *   n_rejected      DEVICE uint64 (8-byte aligned): datagrams rejected.
  * A datagram is accepted when its span lies in the buffer, starts at a
  * multiple of 4, holds the header, carries version 5 and a count of 1..30,
- * and holds count records (bytes after them are ignored).  Enqueues five
- * kernels on `stream` (count, three scan passes, decode).  Errors:
+ * and holds count records (bytes after them are ignored).  Enqueues the
+ * decode kernel on `stream`, for more than 2,048 datagrams a count kernel
+ * before it, and for more than 2,097,152 a scan between the two.  Errors:
  * GNM_E_INVAL (null pointers, misaligned buffer, offsets, counters or
  * workspace, workspace too small, more than 2^31 datagrams), GNM_E_HIP.
  */

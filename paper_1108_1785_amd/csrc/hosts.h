@@ -32,9 +32,9 @@ struct __attribute__((aligned(16))) HostEntry {
 constexpr unsigned long long kHostWide = 1ull << 63;
 
 // Hash of a host: its top bits choose the partition, its low bits the place in
-// a partition's map.  Multiplicative hashing in 32 bits: the odd factors are
-// 2^32 times the golden ratio and the fractions of the square roots of 3 and 2,
-// with the high half folded into the low one before each, as a product's low
+// a partition's map.  Multiplicative hashing in 32 bits: the odd factors are a
+// prime near 2^32 times the fraction of the golden ratio, and 2^32 times the
+// fractions of the square roots of 3 and 2, with the high half folded into the low one before each, as a product's low
 // bits depend on the low bits alone.  (A 64-bit mix of two 64-bit products per
 // bulk flow took the classify kernel 123 us on a 10 M-record window, this 107;
 // 18.2 and 14.6 on 1 M records of 64 sites.)

@@ -7,11 +7,12 @@
 // and hash-table updates with device-scope atomics are bound by the rate of
 // those atomics.  Here the classify kernel only appends one 16-byte entry
 // (host, bytes, duration) per bulk flow of a registered site to its
-// workgroup's staging range, and four kernels finish the job with no
+// workgroup's staging range, and up to four kernels finish the job with no
 // per-flow device atomics:
 //   1. part_count_kernel: per classify workgroup, the number of its entries
 //      in each of P partitions (a partition is the top bits of a hash of the
-//      key, so all entries of a host land in one partition);
+//      key, so all entries of a host land in one partition); left out where
+//      the classify kernel has the LDS to count them as it appends them;
 //   2. part_scan_kernel: for each partition, the offset of every workgroup's
 //      share within the partition (a column prefix sum) and the totals;
 //   3. part_scatter_kernel: every entry to its partition's range;
@@ -21,12 +22,13 @@
 //      flows' buckets).  Up to 2,048 entries (nearly every partition): the
 //      map has 512 slots, the flow count's atomic gives each flow its place
 //      in its host's list, the lists are packed into LDS, and every flow is
-//      ranked within its host's list by a lane (lists beyond 256 flows are
-//      bisected by a wave).  More entries (a hot host): a map of 256 slots
-//      and a radix selection over the 14-bit bucket, four rounds that re-read
-//      the entries, each counting the candidates' next 4-bit digit in 16 LDS
-//      bins per host and keeping the digit where the running count reaches
-//      the rank.
+//      ranked within its host's list by a lane (of longer lists than 256 a
+//      wave finds the median in 7 passes, each leaving a quarter of the
+//      range).  More entries (a hot host): a map of 256 slots and a radix
+//      selection over the 14-bit bucket, four rounds that read the entries,
+//      each counting the candidates' next 4-bit digit in 16 LDS bins per host
+//      and keeping the digit where the running count reaches the rank; the
+//      first also leaves slot and bucket in the entries for the others.
 //      A partition with more hosts than the map holds is done in batches: the
 //      entries of hosts not yet in the map are compacted in place and
 //      reduced by the next batch.
@@ -51,8 +53,8 @@ namespace {
 constexpr uint32_t kHostThreads = 256;  // lanes that reduce one partition
 constexpr uint32_t kHostGroups = 2;     // partitions reduced by one workgroup
 constexpr uint32_t kHostSlots = 256;        // LDS hash-map slots of a large partition (a power of two)
-constexpr uint32_t kListSlots = 512;        // of one whose flow lists fit LDS: the partition rule's mean of 300 or
-                                            // fewer entries, all of different hosts, must not need a second batch
+constexpr uint32_t kListSlots = 512;        // of one whose flow lists fit LDS: a generated window's mean of 200 to 400
+                                            // entries, all of different hosts, must not need a second batch
 constexpr uint32_t kListCap = 2048;         // entries of such a partition
 constexpr uint32_t kListRank = 256;         // flows of a host that are ranked one against the others
 constexpr uint32_t kListSlotBits = 9, kListPlaceBits = 9;
@@ -565,8 +567,10 @@ PartLayout layout(uint64_t n, uint64_t grid) {
 }  // namespace
 
 uint32_t host_part_bits(uint64_t n) {
-  // the power of two nearest n / 2048: a generated window's partitions then
-  // hold about 300 entries of about 130 hosts, half the LDS map
+  // the power of two nearest n / 2048, so 1,448 to 2,896 records a partition:
+  // of generated records, 14% of which are such flows, 200 to 400 entries (344
+  // of 127 hosts at 10 M records), within the LDS map if every one is of
+  // another host
   uint32_t b = kPartBitsMin;
   while (b < kPartBitsMax && (1ull << b) * 2896u <= n) ++b;
   return b;

@@ -16,11 +16,11 @@
 // them all itself (12.3 us a call against 14.0 us with the count kernel at
 // 1,900 datagrams, 12.5 against 14.6 at 360; the call's host side is most of
 // both).
-// The decode is bound by memory, 48 B read and 33 B written per record: 157
-// us for 10 M records, 5.2 TB/s, what a large copy reaches here.  One
+// The decode is bound by memory, 48 B read and 33 B written per record: 149
+// us for 10 M records, 5.5 TB/s, what a large copy reaches here.  One
 // half-wave per datagram with each lane reading its own record (four 8-byte
 // loads, 48 bytes apart) took 197 us: every load touched a line per lane, and
-// the streaming loads fetched lines again.  The count kernel (16 us, one
+// the streaming loads fetched lines again.  The count kernel (12 us, one
 // scattered line per datagram) replaces a count and three scan kernels (32 us).
 // Field layout (public NetFlow version 5 export format, big-endian): header
 // of 24 bytes starting with version u16 and count u16; records of 48 bytes:

@@ -1698,10 +1698,12 @@ uint64_t sized_grid(const gnm_registry *reg, uint64_t n, uint32_t R, uint32_t gr
 
 // Workgroups for an automatic launch of `grid` (a tile each) over n records:
 // two per tile where that leaves CUs idle and the tables are small, so that
-// twice the CUs load half as much each: 300 k records on 64 sites (7 KB a
-// table) 15.9 us with 74 workgroups, 15.5 with 148, 100 k 13.6 and 12.8; on
-// 1,000 sites (112 KB) 300 k take 26.3 with 74 and 27.6 with 128.  Only into
-// work areas that hold that many (a workspace with the tables, and the keys if
+// twice the CUs load half as much each, against twice the tables to merge.  One
+// and two per tile: 64 sites (7.3 KB a table) 100 k records 13.6 and 11.9 us,
+// 300 k 15.6 and 14.9, 600 k 18.0 and 16.6; 140 sites (15.8 KB) 100 k 14.7 and
+// 12.8, 420 k 17.3 and 16.9; 200 sites (22.6 KB) 420 k 17.3 and 17.4, 300 sites
+// (33.8 KB) 100 k 15.0 and 13.4 but 420 k 18.0 and 18.9; 500 sites (56 KB)
+// 300 k 17.1 and 18.7.  Only into work areas that hold that many (a workspace with the tables, and the keys if
 // there are histograms to count; a host table's buffer).
 uint64_t split_tiles(const gnm_registry *reg, uint64_t n, uint64_t grid, uint32_t n_windows, const gnm_params &p,
                      int dev) {
