@@ -526,8 +526,8 @@ def main():
     forms["hosts"] = {"records_per_s": args.steps * n_win / wall_h, "call_ms_avg": hk, "plain_call_ms_avg": k_avg,
                       "overhead_vs_plain": hk / k_avg - 1.0, "table_capacity": host_t.capacity,
                       "hosts_window0": got_hosts[3], "host_flows_window0": got_hosts[4],
-                      "launch": "classify call staging the bulk flows of registered sites, then partition counts, "
-                                "their scan, the scatter and the per-partition reduce (statistics and medians)"}
+                      "launch": "classify call staging the bulk flows of registered sites and counting them per partition, then "
+                                "the counts' scan, the scatter and the per-partition reduce (statistics and medians)"}
     log("hosts: classify call with per-host statistics and medians %.4f ms (plain %.4f), %d hosts in window 0" %
         (hk, k_avg, got_hosts[3]))
     del host_t

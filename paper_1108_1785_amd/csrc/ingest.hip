@@ -14,14 +14,15 @@
 //      coalesced stores, lane i decoding record i of the tile.
 // Up to 2,048 datagrams need no first kernel: every decode workgroup counts
 // them all itself (12.3 us a call against 14.0 us with the count kernel at
-// 1,900 datagrams, 12.5 against 14.6 at 360; the call's host side is most of
-// both).
+// 1,900 datagrams, 12.5 against 14.6 at 360, with a host side of the call, most
+// of both, that was 4 us longer than now: 8.5 at 351).
 // The decode is bound by memory, 48 B read and 33 B written per record: 149
-// us for 10 M records, 5.5 TB/s, what a large copy reaches here.  One
-// half-wave per datagram with each lane reading its own record (four 8-byte
-// loads, 48 bytes apart) took 197 us: every load touched a line per lane, and
-// the streaming loads fetched lines again.  The count kernel (12 us, one
-// scattered line per datagram) replaces a count and three scan kernels (32 us).
+// to 157 us (two cards) for 10 M records, 5.2 to 5.5 TB/s, what a large copy
+// reaches here.  One half-wave per datagram with each lane reading its own
+// record (four 8-byte loads, 48 bytes apart) took 197 us: every load touched a
+// line per lane, and the streaming loads fetched lines again.  The count kernel
+// (12 us, one scattered line per datagram) replaces a count and three scan
+// kernels (32 us).
 // Field layout (public NetFlow version 5 export format, big-endian): header
 // of 24 bytes starting with version u16 and count u16; records of 48 bytes:
 // srcaddr, dstaddr, nexthop u32; input, output u16; dPkts, dOctets, First,

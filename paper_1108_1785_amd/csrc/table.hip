@@ -23,8 +23,8 @@
 // bytes in the order they came, ordered by three partition kernels (counts,
 // scan, scatter) that read and wrote all of them twice more, took 1,179 + 131
 // + 5 + 447 + 184 us for 10 windows of 10 M records and 20,000 sites; lying by
-// tile as they are written they take 1,289 + 144 us (24-byte entries, two
-// stores each: 1,335 + 193).  Tiles of 512 or 1,024 rows (fewer, denser parts)
+// tile as they are written they took 1,289 + 144 us (24-byte entries, two
+// stores each: 1,335 + 193), now 1,251 + 100.  Tiles of 512 or 1,024 rows (fewer, denser parts)
 // gain 5 to 10 % there and lose 8 to 25 % on one window, whose merge then has
 // too few workgroups.
 // With parts alone, what did not fit went to device atomics.  One window of 10 M
