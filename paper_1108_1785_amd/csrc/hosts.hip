@@ -402,10 +402,10 @@ __device__ __forceinline__ void reduce_lists(ListMap &m, Shared &sh, const Parts
 
 // One batch of a larger partition (a hot host): every digit round re-reads
 // the entries.  The first pass leaves slot << 14 | bucket in place of the
-// duration in those that found a slot, so that the
-// rounds need neither the rate again (1 M records, half of them one host's:
-// 1,026 us a call with a division in every round, 770 now) nor, unless some
-// found none, the map.  A lane always reads the same entries.
+// duration in those that found a slot, so that the rounds need neither the rate
+// again (1 M records, half of them one host's: 1,026 us a call with a division
+// in every round, 770 now) nor, unless some found none, the map.  A lane always
+// reads the same entries.
 __device__ __forceinline__ void reduce_radix(HostMap &m, Shared &sh, const Parts &q, HostEntry *ent, uint32_t n,
                                              uint32_t nmax, uint32_t g) {
   static_assert(kHostSlots == kHostThreads, "one map slot per thread");
@@ -518,9 +518,10 @@ __device__ __forceinline__ void reduce_radix(HostMap &m, Shared &sh, const Parts
 // batches of the radix selection.
 // A window of 10 M records (4,096 partitions of 344 entries, 127 hosts) is
 // bound by the latency of a workgroup's steps and by the one counter (entries
-// of half the size, as now, changed nothing): 61.7 us with a radix selection for every partition; with lists 67 us at one
-// partition per workgroup (42 without the counter's atomics), 51.7 at two,
-// 56 at four (whose barriers wait for the slowest of four).  One of 1 M
+// of half the size, as now, changed nothing): 61.7 us with a radix selection for
+// every partition; with lists 67 us at one partition per workgroup (42 without
+// the counter's atomics), 51.7 at two (50 now), 56 at four (whose barriers wait
+// for the slowest of four).  One of 1 M
 // records of the 64-site registry (512 partitions of 275 entries, nearly as
 // many hosts): 49 us when its hosts overflowed a map of 256 slots, 11.7 now.
 __global__ __launch_bounds__(kHostThreads * kHostGroups) void host_reduce_kernel(const Parts q) {

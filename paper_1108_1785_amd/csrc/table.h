@@ -151,9 +151,10 @@ struct TableFlags {
 };
 
 // Enqueue the merge after the classify kernel: one workgroup per (window,
-// tile), and more for tiles with many entries, that add their sums into acc (initialised before the classify kernel,
-// or accumulated into) and writes the flags.  window_offsets: as the classify
-// kernel got them (NULL: one window); tile_bits: as it had.
+// tile), and more for tiles with many entries, which add their sums into acc
+// (initialised before the classify kernel, or accumulated into) and write the
+// flags.  window_offsets: as the classify kernel got them (NULL: one window);
+// tile_bits: as it had.
 int table_merge_launch(void *work, uint64_t n, uint64_t grid, const uint64_t *window_offsets, uint32_t n_windows,
                        uint32_t rows, uint32_t tile_bits, uint32_t slots, const BulkRule &bulk, unsigned long long *acc,
                        const TableFlags &fl, hipStream_t stream);
